@@ -115,3 +115,25 @@ def test_refined_solve_with_nufft_operator(refine):
     e = rel(c.cpu().numpy(), ref)
     print(f"refine {refine} with the NUFFT operator: {e:.2e} ({si['iterations']} its)")
     assert e < 1e-10
+
+
+@pytest.mark.parametrize("nx,ny,M,leaf,tol", [
+    (64, 64, 9000, 64, 1e-13),    # one box of 128 cells: several windows, chunks inside a box
+    (40, 40, 5000, 40, 1e-2),     # narrow kernel, the window edge inside the box
+    (256, 4, 1100, 16, 1e-9),     # boxes narrower than a cell, a grid narrower than a window
+    (16, 16, 257, 16, 1e-12),     # a single box, one point past the batches
+    (96, 64, 7000, 8, 1e-12),     # many runs of a few points in a chunk
+])
+def test_spreading_boxes(nx, ny, M, leaf, tol):
+    """Type 1 over box shapes, windows and runs, points clustered so that box
+    populations differ, within the transform's 10 tol (as above)."""
+    rng = np.random.default_rng(40)
+    pts = rng.random((M, 2))
+    pts[: M // 3] = 0.37 + 0.01 * pts[: M // 3]
+    pts[0] = 0.0
+    F = complex_normal(rng, (2, M))
+    plan = nd.Plan(pts, nx, ny, leaf=leaf)
+    c = plan.nufft_adj(torch.from_numpy(F).to(DEV), tol).cpu().numpy()
+    plan.close()
+    ref = onu.apply_adj(pts, F, nx, ny)
+    assert max(rel(c[i], ref[i]) for i in range(2)) < 10 * tol
