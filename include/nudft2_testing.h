@@ -87,6 +87,10 @@ nudft2_status nudft2_test_gemm_cfg(int32_t prec, int32_t opA, int32_t opB, int32
                                    int32_t splits, float* ms);
 nudft2_status nudft2_test_geqrf(int32_t prec, int32_t nb, const int32_t* mn,
                                 const int32_t* ld, const int64_t* ptrs);
+/* the same for lists expected to hold nearly dependent columns (the first
+ * recompression stage's): the same factors, other launches */
+nudft2_status nudft2_test_geqrf_graded(int32_t prec, int32_t nb, const int32_t* mn,
+                                       const int32_t* ld, const int64_t* ptrs);
 nudft2_status nudft2_test_ormqr(int32_t prec, int32_t trans, int32_t nb,
                                 const int32_t* dims, const int32_t* ld,
                                 const int64_t* ptrs);

@@ -116,6 +116,7 @@ def _load():
                                            I32P, I64P, C.c_double, C.c_double, C.c_double,
                                            C.c_int32, C.POINTER(C.c_float)]),
         "nudft2_test_geqrf": (C.c_int, [C.c_int32, C.c_int32, I32P, I32P, I64P]),
+        "nudft2_test_geqrf_graded": (C.c_int, [C.c_int32, C.c_int32, I32P, I32P, I64P]),
         "nudft2_test_ormqr": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, I32P, I32P, I64P]),
         "nudft2_test_pchol": (C.c_int, [C.c_int32, I32P, I32P, I64P, C.c_double, I32P, I32P]),
         "nudft2_test_trsv": (C.c_int, [C.c_int32, C.c_int32, I32P, I32P, I64P, C.c_int32]),

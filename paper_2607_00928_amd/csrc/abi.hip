@@ -164,7 +164,8 @@ static void test_gemm(int opA, int opB, int nb, const int32_t* mnk, const int32_
 }
 
 template <typename T>
-static void test_geqrf(int nb, const int32_t* mn, const int32_t* ld, const int64_t* ptrs) {
+static void test_geqrf(int nb, const int32_t* mn, const int32_t* ld, const int64_t* ptrs,
+                       bool graded) {
   std::vector<QRDesc<T>> d(nb);
   for (int i = 0; i < nb; ++i)
     d[i] = QRDesc<T>{mn[2 * i], mn[2 * i + 1], ld[2 * i], ld[2 * i + 1], (cplx<T>*)ptrs[3 * i],
@@ -173,7 +174,7 @@ static void test_geqrf(int nb, const int32_t* mn, const int32_t* ld, const int64
   pool.init(16 << 20, nullptr);
   void* ws;
   ND_HIP(hipMalloc(&ws, qr_workspace<T>(d)));
-  geqrf_batched<T>(pool, d, ws);
+  geqrf_batched<T>(pool, d, ws, graded);
   pool.sync_reset();
   ND_HIP(hipFree(ws));
 }
@@ -505,15 +506,25 @@ nudft2_status nudft2_test_gemm_cfg(int32_t prec, int32_t opA, int32_t opB, int32
   });
 }
 
-nudft2_status nudft2_test_geqrf(int32_t prec, int32_t nb, const int32_t* mn, const int32_t* ld,
-                                const int64_t* ptrs) {
+static nudft2_status test_geqrf_any(int32_t prec, int32_t nb, const int32_t* mn, const int32_t* ld,
+                                    const int64_t* ptrs, bool graded) {
   return guard([&] {
     ND_CHECK(mn && ld && ptrs && nb > 0, NUDFT2_E_INVAL, "bad arguments");
     need_device();
     TestPrec tp(prec);
-    if (prec == 0) test_geqrf<double>(nb, mn, ld, ptrs);
-    else test_geqrf<float>(nb, mn, ld, ptrs);
+    if (prec == 0) test_geqrf<double>(nb, mn, ld, ptrs, graded);
+    else test_geqrf<float>(nb, mn, ld, ptrs, graded);
   });
+}
+
+nudft2_status nudft2_test_geqrf(int32_t prec, int32_t nb, const int32_t* mn, const int32_t* ld,
+                                const int64_t* ptrs) {
+  return test_geqrf_any(prec, nb, mn, ld, ptrs, false);
+}
+
+nudft2_status nudft2_test_geqrf_graded(int32_t prec, int32_t nb, const int32_t* mn,
+                                       const int32_t* ld, const int64_t* ptrs) {
+  return test_geqrf_any(prec, nb, mn, ld, ptrs, true);
 }
 
 nudft2_status nudft2_test_ormqr(int32_t prec, int32_t trans, int32_t nb, const int32_t* dims,

@@ -181,9 +181,10 @@ struct HSS2 : HSSBase {
 
 // Orthonormal basis Q (m x min(m,c)) of the columns of each A (destroyed);
 // optionally the triangular factors into Rout (caller-allocated, k x c).
+// graded: as geqrf_batched.
 template <typename T>
 void orth(Ctx& cx, std::vector<Mat<T>>& A, std::vector<Mat<T>>& Q,
-          std::vector<Mat<T>>* Rout = nullptr);
+          std::vector<Mat<T>>* Rout = nullptr, bool graded = false);
 
 struct PcholOut {
   Mat<double> L;

@@ -447,7 +447,7 @@ void build_2d(Ctx& cx, const std::vector<Tree1>& tx, const std::vector<Tree1>& t
       }
       {
         ProfSite orth_site_(PS_S1_QR);
-        orth<T>(cx, A, Q, &R);
+        orth<T>(cx, A, Q, &R, true);
       }
       A.clear(); Q.clear(); R.clear();
       ND_HIP(hipStreamSynchronize(cx.s));
@@ -607,7 +607,7 @@ void build_2d(Ctx& cx, const std::vector<Tree1>& tx, const std::vector<Tree1>& t
           }
           {
             ProfSite orth_site_(PS_S1_QR);
-            orth<T>(cx, A, Q, &R);
+            orth<T>(cx, A, Q, &R, true);
           }
           bd.own(p, l, Builder<T>::K_F, cf, old);
           bd.own(p, lc, Builder<T>::K_R, cq, old);

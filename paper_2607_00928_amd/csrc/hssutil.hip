@@ -10,7 +10,7 @@ namespace nd {
 // optionally the triangular factor (k x c) into Rout (caller-allocated).
 template <typename T>
 void orth(Ctx& cx, std::vector<Mat<T>>& A, std::vector<Mat<T>>& Q,
-          std::vector<Mat<T>>* Rout) {
+          std::vector<Mat<T>>* Rout, bool graded) {
   if (A.empty()) return;
   std::vector<QRDesc<T>> qd;
   std::vector<Mat<T>> Rb(A.size()), Tb(A.size());
@@ -28,7 +28,7 @@ void orth(Ctx& cx, std::vector<Mat<T>>& A, std::vector<Mat<T>>& Q,
   for (size_t i = 0; i < A.size(); ++i)
     qd.push_back({A[i].r, A[i].c, A[i].ld, Rb[i].ld, A[i].p, Rb[i].p, Tb[i].p});
   void* ws = cx.tmp_alloc(qr_workspace<T>(qd));
-  geqrf_batched<T>(cx.pool, qd, ws);
+  geqrf_batched<T>(cx.pool, qd, ws, graded);
   std::vector<FillDesc<T>> fd;
   std::vector<OrmDesc<T>> od;
   std::vector<CopyDesc<T, T>> cd;
@@ -44,9 +44,9 @@ void orth(Ctx& cx, std::vector<Mat<T>>& A, std::vector<Mat<T>>& Q,
   if (Rout) copy_batched<T, T>(cx.pool, cd);
 }
 template void orth<float>(Ctx&, std::vector<Mat<float>>&, std::vector<Mat<float>>&,
-                          std::vector<Mat<float>>*);
+                          std::vector<Mat<float>>*, bool);
 template void orth<double>(Ctx&, std::vector<Mat<double>>&, std::vector<Mat<double>>&,
-                           std::vector<Mat<double>>*);
+                           std::vector<Mat<double>>*, bool);
 
 // Pivoted Cholesky of a batch of FP64 Grams (w x w, ld w); returns ranks on
 // the host.  K is destroyed.

@@ -112,11 +112,13 @@ void gemm_batched(DescPool& pool, const std::vector<GemmDesc<T>>& d, Op opA, Op 
 // = Q_0 Q_1 ..., Q_b = I - V_b T_b V_b^H).  Block b has kb = min(QR_OB, kmin -
 // QR_OB b) columns; its T_b (kb x kb, leading dimension kb) starts at
 // Tb + QR_OB^2 b; qr_tsize gives the element count.  The factorization runs in
-// QR_NB-column panels (one cooperative launch each) whose updates stay inside
-// their half of the block (QR_HB columns); the left half's reflectors then
+// QR_NB-column panels (FP64: one cooperative launch each; FP32: from Gram
+// matrices, qr_half.h) whose updates stay inside their half of the block
+// (QR_HB columns); the left half's reflectors then
 // update the right half, the block's T joins the two halves' factors, and the
 // trailing columns are updated once per block.
-// ws: workspace (see qr_workspace).
+// ws: workspace (see qr_workspace).  graded: many panels are expected to hold
+// columns nearly dependent on earlier ones (a hint for speed only).
 constexpr int QR_NB = 32;
 constexpr int QR_OB = 256;
 constexpr int QR_HB = 128;   // the two halves of a block (see geqrf_batched)
@@ -141,7 +143,8 @@ inline int64_t qr_tsize(int m, int n) {
 template <typename T>
 size_t qr_workspace(const std::vector<QRDesc<T>>& d);   // bytes
 template <typename T>
-void geqrf_batched(DescPool& pool, const std::vector<QRDesc<T>>& d, void* ws);
+void geqrf_batched(DescPool& pool, const std::vector<QRDesc<T>>& d, void* ws,
+                   bool graded = false);
 
 // Apply Q (trans = false) or Q^H (trans = true) of a QR from geqrf_batched to
 // C (m x nc, ldc) from the left, in place.  Only the first `kuse` reflectors

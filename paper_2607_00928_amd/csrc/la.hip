@@ -1289,7 +1289,7 @@ __global__ void gemm_prescale_kernel(DS descs) {
 // compact-WY factor T (Q_panel = I - V T V^H) and the explicit V / R split
 // described in la.h.
 //
-// Panel factorization: a group of gsize workgroups factors one problem's
+// FP64 panel factorization (FP32 panels: qr_half.h): a group of gsize workgroups factors one problem's
 // panel; workgroup w of the group holds panel rows [w 128 R, (w+1) 128 R)
 // in registers.  Wave v of a workgroup owns the column group v / 2 (QP_CG
 // consecutive columns) on the row half v % 2; lane l of it holds rows
@@ -1348,47 +1348,12 @@ __device__ inline cplx<T> ld_agent(const cplx<T>* p) {
                __hip_atomic_load(&p->y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// FP32 exchange words: a float and the column step's tag in one 64-bit
-// agent-scope atomic word, so a reader that sees the tag sees the value (no
-// fence, no separate counter).
-__device__ inline void st_tagged(unsigned long long* p, float v, unsigned tag) {
-  const unsigned long long w = (unsigned long long)__float_as_uint(v) |
-                               ((unsigned long long)tag << 32);
-  __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline unsigned long long ld_tagged(const unsigned long long* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// wait until the two words at p carry tag (bounded; sets err on timeout and
-// gives up at once when err is already set) and return their values
-__device__ inline float2 wait_tagged2(const unsigned long long* p, unsigned tag, int* err) {
-  unsigned long long a = ld_tagged(p), b = ld_tagged(p + 1);
-  unsigned it = 0;
-  while ((unsigned)(a >> 32) != tag || (unsigned)(b >> 32) != tag) {
-    if ((++it & 255) == 0 &&
-        (it > (1u << 20) || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-      atomicExch(err, 1);
-      break;
-    }
-    __builtin_amdgcn_s_sleep(1);
-    a = ld_tagged(p);
-    b = ld_tagged(p + 1);
-  }
-  return make_float2(__uint_as_float((unsigned)a), __uint_as_float((unsigned)b));
-}
-// FP32 group scratch: two sets (by column-step parity) of gsize partial-sum
-// rows and one pivot row, each QR_NB complex values as tagged word pairs
-__host__ __device__ inline size_t qp_tag_words(int gsize) {
-  return (size_t)2 * (gsize + 1) * QR_NB * 2;
-}
-
 constexpr int QS = QR_NB + 1;          // rotating sum slots per column
 constexpr int QSCR = 3 * QS + 3 * QR_NB;   // rotating sums + rotating row copies
 constexpr int QP_NT = 1024;            // threads of a panel workgroup
 constexpr int QP_CG = 4;               // columns per thread
-// rows per lane: 4 x 4 complex FP32 or 2 x 4 complex FP64 values (32 VGPRs)
+// rows per lane: 2 x 4 complex FP64 values (32 VGPRs)
 template <typename T> struct QPanel { static constexpr int R = 2; };
-template <> struct QPanel<float> { static constexpr int R = 4; };
 
 // sum over the 64 lanes of a wave, valid in lane 63 (all lanes active)
 template <typename T>
@@ -1418,7 +1383,6 @@ __global__ __launch_bounds__(QP_NT) void qr_panel_kernel(
   __shared__ C2 tot[QR_NB];              // (gsize > 1) group column sums
   __shared__ C2 rowv[QR_NB];             // row jj
   __shared__ C2 Ts[QR_NB][QR_NB + 1];
-  __shared__ C2 red[QP_NT / QR_NB][QR_NB];   // (FP32, gsize > 1) partial sums of the group
   const int ngroups = gridDim.x / gsize;
   const int g = blockIdx.x / gsize, w = blockIdx.x % gsize;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1476,52 +1440,7 @@ __global__ __launch_bounds__(QP_NT) void qr_panel_kernel(
         for (int l = 0; l < QP_CG; ++l) rowv[c0 + l] = a[0][l];
       }
       __syncthreads();
-      if constexpr (sizeof(T) == 4) {
-        if (gsize > 1) {
-          // publish this workgroup's sums (and, from workgroup 0, row jj) as
-          // tagged words; every workgroup reads all of them: thread (j, c)
-          // adds the partials of workgroups j, j + 32, ... for column c, then
-          // the 32 partials per column are added in a fixed order
-          unsigned long long* tg = (unsigned long long*)scratch + (size_t)g * qp_tag_words(gsize);
-          unsigned long long* part = tg + (size_t)(step & 1) * (gsize + 1) * QR_NB * 2;
-          unsigned long long* rowp = part + (size_t)gsize * QR_NB * 2;
-          const unsigned tag = (unsigned)step + 1;
-          if (tid < QR_NB) {
-            unsigned long long* q = part + ((size_t)w * QR_NB + tid) * 2;
-            st_tagged(q, sp[0][tid].x + sp[1][tid].x, tag);
-            st_tagged(q + 1, sp[0][tid].y + sp[1][tid].y, tag);
-          }
-          if (row_owner) {
-#pragma unroll
-            for (int l = 0; l < QP_CG; ++l) {
-              st_tagged(rowp + (c0 + l) * 2, (float)a[0][l].x, tag);
-              st_tagged(rowp + (c0 + l) * 2 + 1, (float)a[0][l].y, tag);
-            }
-          }
-          const int cj = tid % QR_NB, jj2 = tid / QR_NB;
-          float vr = 0.f, vi = 0.f;
-          for (int w2 = jj2; w2 < gsize; w2 += QP_NT / QR_NB) {
-            const float2 v = wait_tagged2(part + ((size_t)w2 * QR_NB + cj) * 2, tag, err);
-            vr += v.x;
-            vi += v.y;
-          }
-          red[jj2][cj] = mk<T>(vr, vi);
-          if (jj2 == 0) {
-            const float2 v = wait_tagged2(rowp + cj * 2, tag, err);
-            rowv[cj] = mk<T>(v.x, v.y);
-          }
-          __syncthreads();
-          if (tid < QR_NB) {
-            T tr = 0, ti = 0;
-            for (int j2 = 0; j2 < QP_NT / QR_NB; ++j2) {
-              tr += red[j2][tid].x;
-              ti += red[j2][tid].y;
-            }
-            tot[tid] = mk<T>(tr, ti);
-          }
-          __syncthreads();
-        }
-      } else if (gsize > 1) {
+      if (gsize > 1) {
         C2* buf = sums + (step % 3) * QS;
         C2* rbuf = rows + (step % 3) * QR_NB;
         if (tid < QR_NB) {
@@ -2595,17 +2514,15 @@ void qr_panel_launch(DescPool& pool, const QRDesc<T>* dd, const std::vector<int>
   // Twice the rows per workgroup (RM = 2): for panels taller than the device
   // holds otherwise, and for multi-workgroup panels when the halved groups
   // still fill every CU (many problems): fewer workgroups exchange column
-  // sums, which outweighs the spilled registers (1024 leaf panels of
-  // 1024 x 430: 42.5 -> 32.1 ms FP32; 1024 x 500 x 300 FP64: 32.6 -> 23.7 ms);
-  // with few tall problems the halved group count leaves CUs idle (16 x 5000:
-  // 7.4 -> 7.9 ms), so those keep RM = 1.
+  // sums, which outweighs the spilled registers (1024 x 500 x 300 FP64: 32.6
+  // -> 23.7 ms); with few tall problems the halved group count leaves CUs idle,
+  // so those keep RM = 1.
   const int gsize2 = std::max(1, (maxmr + 2 * rows - 1) / (2 * rows));
   const bool tall = gsize > mres || (gsize > 1 && (int64_t)nact * gsize2 >= mres);
   if (tall) gsize = gsize2;
   ND_CHECK(gsize <= mres, NUDFT2_E_INTERNAL, "QR panel taller than the device can hold");
   int ngroups = std::max(1, std::min(nact, mres / gsize));
-  const size_t per_group = sizeof(T) == 4 ? qp_tag_words(gsize) * sizeof(unsigned long long)
-                                           : QSCR * sizeof(cplx<T>);
+  const size_t per_group = QSCR * sizeof(cplx<T>);
   const size_t scr_bytes = ((size_t)ngroups * per_group + 255) & ~size_t(255);
   const size_t words = (scr_bytes + (size_t)ngroups * sizeof(unsigned)) / sizeof(unsigned);
   char* z = (char*)pool.reserve(words * sizeof(unsigned));
@@ -2624,6 +2541,10 @@ void qr_panel_launch(DescPool& pool, const QRDesc<T>* dd, const std::vector<int>
   });
 }
 
+}  // namespace nd
+#include "qr_half.h"
+namespace nd {
+
 // per problem: W and W2 (QR_OB x n), S (QR_OB x QR_OB), the panels' factors
 // (QR_OB / QR_NB blocks of QR_NB x QR_NB)
 template <typename T>
@@ -2635,7 +2556,7 @@ size_t qr_workspace(const std::vector<QRDesc<T>>& d) {
 }
 
 template <typename T>
-void geqrf_batched(DescPool& pool, const std::vector<QRDesc<T>>& din, void* ws) {
+void geqrf_batched(DescPool& pool, const std::vector<QRDesc<T>>& din, void* ws, bool graded) {
   if (din.empty()) return;
   if (hazards_enabled()) {
     std::vector<Region> v;
@@ -2680,32 +2601,39 @@ void geqrf_batched(DescPool& pool, const std::vector<QRDesc<T>>& din, void* ws) 
   for (int J0 = 0; J0 < kmax; J0 += QR_OB) {
     const int bidx = J0 / QR_OB;
     for (int H0 = J0; H0 < std::min(J0 + QR_OB, kmax); H0 += QR_HB) {
-      for (int j0 = H0; j0 < std::min(H0 + QR_HB, kmax); j0 += QR_NB) {
+      if constexpr (std::is_same<T, float>::value) {
         act.clear();
-        g1.clear(); g2.clear(); g3.clear();
-        for (int i = 0; i < nb; ++i) {
-          const QRDesc<T>& q = d[i];
-          int kmin = qr_kmin(q.m, q.n);
-          if (kmin <= j0) continue;
-          act.push_back(i);
-          int jb = std::min(QR_NB, kmin - j0);
-          int nt = std::min(q.n, H0 + QR_HB) - j0 - jb;
-          if (nt <= 0) continue;
-          int mr = q.m - j0;
-          cplx<T>* V = q.A + j0 + (int64_t)j0 * q.lda;
-          cplx<T>* At = q.A + j0 + (int64_t)(j0 + jb) * q.lda;
-          cplx<T>* Tj = q.Tw + (int64_t)((j0 % QR_OB) / QR_NB) * QR_NB * QR_NB;
-          // V unit lower trapezoidal, T upper triangular
-          g1.push_back({jb, nt, mr, q.lda, q.lda, QR_NB, V, At, W[i], T(1), T(0), T(0), 0, 1});
-          g2.push_back({jb, nt, jb, QR_NB, QR_NB, QR_NB, Tj, W[i], W2[i], T(1), T(0), T(0), 0, 2});
-          g3.push_back({mr, nt, jb, q.lda, QR_NB, q.lda, V, W2[i], At, T(-1), T(0), T(1), 0, 1});
+        for (int i = 0; i < nb; ++i)
+          if (qr_kmin(d[i].m, d[i].n) > H0) act.push_back(i);
+        qr_half_panels(pool, dd, d, act, H0, graded);
+      } else {
+        for (int j0 = H0; j0 < std::min(H0 + QR_HB, kmax); j0 += QR_NB) {
+          act.clear();
+          g1.clear(); g2.clear(); g3.clear();
+          for (int i = 0; i < nb; ++i) {
+            const QRDesc<T>& q = d[i];
+            int kmin = qr_kmin(q.m, q.n);
+            if (kmin <= j0) continue;
+            act.push_back(i);
+            int jb = std::min(QR_NB, kmin - j0);
+            int nt = std::min(q.n, H0 + QR_HB) - j0 - jb;
+            if (nt <= 0) continue;
+            int mr = q.m - j0;
+            cplx<T>* V = q.A + j0 + (int64_t)j0 * q.lda;
+            cplx<T>* At = q.A + j0 + (int64_t)(j0 + jb) * q.lda;
+            cplx<T>* Tj = q.Tw + (int64_t)((j0 % QR_OB) / QR_NB) * QR_NB * QR_NB;
+            // V unit lower trapezoidal, T upper triangular
+            g1.push_back({jb, nt, mr, q.lda, q.lda, QR_NB, V, At, W[i], T(1), T(0), T(0), 0, 1});
+            g2.push_back({jb, nt, jb, QR_NB, QR_NB, QR_NB, Tj, W[i], W2[i], T(1), T(0), T(0), 0, 2});
+            g3.push_back({mr, nt, jb, q.lda, QR_NB, q.lda, V, W2[i], At, T(-1), T(0), T(1), 0, 1});
+          }
+          int maxmr = 0;
+          for (int i : act) maxmr = std::max(maxmr, d[i].m - j0);
+          qr_panel_launch<T>(pool, dd, act, j0, maxmr);
+          gemm_batched<T>(pool, g1, OpC, OpN);
+          gemm_batched<T>(pool, g2, OpC, OpN);
+          gemm_batched<T>(pool, g3, OpN, OpN);
         }
-        int maxmr = 0;
-        for (int i : act) maxmr = std::max(maxmr, d[i].m - j0);
-        qr_panel_launch<T>(pool, dd, act, j0, maxmr);
-        gemm_batched<T>(pool, g1, OpC, OpN);
-        gemm_batched<T>(pool, g2, OpC, OpN);
-        gemm_batched<T>(pool, g3, OpN, OpN);
       }
       // the half's factor T_h (in its place inside the block's T) from the
       // panels' factors and S = V_h^H V_h
@@ -3146,7 +3074,7 @@ void fill_batched(DescPool& pool, const std::vector<FillDesc<T>>& d) {
 #define INST(T)                                                                          \
   template void gemm_batched<T>(DescPool&, const std::vector<GemmDesc<T>>&, Op, Op, int);\
   template size_t qr_workspace<T>(const std::vector<QRDesc<T>>&);                        \
-  template void geqrf_batched<T>(DescPool&, const std::vector<QRDesc<T>>&, void*);       \
+  template void geqrf_batched<T>(DescPool&, const std::vector<QRDesc<T>>&, void*, bool); \
   template size_t orm_workspace<T>(const std::vector<OrmDesc<T>>&);                      \
   template void ormqr_batched<T>(DescPool&, const std::vector<OrmDesc<T>>&, bool, void*, bool); \
   template void trsv_upper_batched<T>(DescPool&, const std::vector<TrsDesc<T>>&, bool);  \

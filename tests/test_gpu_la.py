@@ -910,3 +910,84 @@ def test_trtri_inverts_upper_triangles(prec):
         print(f"trtri k={k} prec{prec}: {err:.1e}")
         assert np.abs(np.tril(got, -1)).max() == 0
         assert err < (1e-13 if prec == 0 else 2e-5) * max(1.0, np.log2(k))
+
+
+@pytest.mark.parametrize("graded", [False, True])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_geqrf_dependent_columns(prec, graded):
+    """QR of panels whose columns fall far below their norm against the
+    earlier ones (where the FP32 panels split): numerical rank below the
+    column count, repeated and zero columns, steeply graded columns, columns
+    that differ by a small multiple of an earlier one, beside a well
+    conditioned problem; m at the row pass's edges.  Q R = A column by column
+    relative to the column's norm, Q unitary, both to rounding as in
+    test_geqrf_ormqr."""
+    rng = np.random.default_rng(700 + prec)
+    eps = 1e-15 if prec == 0 else 6e-8
+    mats = []
+    for m, n, r in [(353, 160, 20), (64, 48, 5), (1100, 96, 40), (129, 129, 60), (40, 200, 33)]:
+        A = crandn(rng, m, r) @ crandn(rng, r, n) / r ** 0.5
+        mats.append(A + 4 * eps * crandn(rng, m, n))
+    A = crandn(rng, 500, 130)
+    A[:, 7] = A[:, 3]
+    A[:, 40] = 0
+    A[:, 41] = 2j * A[:, 2] + 3 * A[:, 39]
+    A[:, 100:] = A[:, :30]
+    mats.append(A)
+    A = crandn(rng, 193, 64)
+    mats.append(A * 10.0 ** (-np.arange(64) % 9))
+    B = crandn(rng, 700, 70)
+    for j in range(1, 70):
+        B[:, j] = B[:, j - 1] + 10.0 ** -(j % 8) * B[:, j]
+    mats.append(B)
+    # a half lost per column: norms fall slowly, the panel's digits add up
+    D = crandn(rng, 900, 130)
+    for j in range(1, 130):
+        D[:, j] = D[:, j - 1] + 0.6 * D[:, j]
+    mats.append(D @ (np.eye(130) - 0.9 * np.eye(130, k=1)))
+    i = np.arange(400)[:, None] / 400
+    mats.append(1 / (i + np.arange(100) / 100 + 0.01 + 0.002j))   # Cauchy-like
+    mats.append(crandn(rng, 300, 97))
+    keep, data, mn, ld, ptr = [], [], [], [], []
+    for A in mats:
+        m, n = A.shape
+        k = min(m, n)
+        nob = (k + QB - 1) // QB
+        tA = to_dev(A, prec)
+        A = from_dev(tA, m, n).astype(np.complex128)   # as rounded
+        tR = torch.full((n, k), 7.0 - 3.0j, dtype=CT[prec][1], device=DEV)
+        tT = torch.full((QB * QB * (nob - 1) + (k - QB * (nob - 1)) ** 2,), 5.0 + 1.0j,
+                        dtype=CT[prec][1], device=DEV)
+        keep += [tA, tR, tT]
+        data.append((A, tA, tR, tT))
+        mn += [m, n]
+        ld += [m, k]
+        ptr += [t.data_ptr() for t in (tA, tR, tT)]
+    a1, p1 = i32(mn)
+    a2, p2 = i32(ld)
+    a3, p3 = i64(ptr)
+    geqrf = lib.nudft2_test_geqrf_graded if graded else lib.nudft2_test_geqrf
+    assert geqrf(prec, len(mats), p1, p2, p3) == 0, lib.nudft2_last_error()
+    dims, ld2, ptr2, Qs = [], [], [], []
+    for A, tA, tR, tT in data:
+        m, n = A.shape
+        tQ = to_dev(np.eye(m), prec)
+        Qs.append(tQ)
+        dims += [m, min(m, n), m]
+        ld2 += [m, m]
+        ptr2 += [tA.data_ptr(), tT.data_ptr(), tQ.data_ptr()]
+    b1, q1 = i32(dims)
+    b2, q2 = i32(ld2)
+    b3, q3 = i64(ptr2)
+    assert lib.nudft2_test_ormqr(prec, 0, len(mats), q1, q2, q3) == 0, lib.nudft2_last_error()
+    for i, ((A, tA, tR, tT), tQ) in enumerate(zip(data, Qs)):
+        m, n = A.shape
+        k = min(m, n)
+        Q, R = from_dev(tQ, m, m).astype(np.complex128), from_dev(tR, k, n).astype(np.complex128)
+        assert np.abs(np.tril(R, -1)).max() == 0
+        cn = np.linalg.norm(A, axis=0)
+        err = (np.linalg.norm(Q[:, :k] @ R - A, axis=0) / np.where(cn > 0, cn, 1)).max()
+        orth = np.abs(Q.conj().T @ Q - np.eye(m)).max()
+        print(f"dependent qr {i} {m}x{n} prec{prec}: recon {err:.1e} orth {orth:.1e}")
+        assert err < 50 * TOL[prec] * np.sqrt(m)
+        assert orth < 50 * TOL[prec] * np.sqrt(m)
