@@ -670,7 +670,13 @@ void build_2d(Ctx& cx, const std::vector<Tree1>& tx, const std::vector<Tree1>& t
       std::vector<Mat<double>> KU(nodes.size()), KV(nodes.size());
       auto form_grams = [&](auto tag) {
         using G = decltype(tag);
-        // a block in the Gram precision: the block itself or a converted copy
+        // a block in the Gram precision: the block itself or a converted copy,
+        // one per block (a coupling is used by both its siblings, a weight T by
+        // the parent's children).  All copies of a level go in one launch below:
+        // a launch each, of some 5 us and as long a gap, was 17 of the 190 ms of
+        // the factorization at 200 x 130, M = 1.5 N, eps = 1e-3.
+        std::vector<CopyDesc<G, T>> cvt;
+        std::map<const void*, Mat<G>> done;
         auto conv = [&](const Mat<T>& m) -> Mat<G> {
           Mat<G> o;
           o.r = m.r;
@@ -679,33 +685,18 @@ void build_2d(Ctx& cx, const std::vector<Tree1>& tx, const std::vector<Tree1>& t
             o.p = m.p;
             o.ld = m.ld;
           } else {
+            if (m.r > 0 && m.c > 0) {
+              auto it = done.find(m.p);
+              if (it != done.end()) return it->second;
+            }
             o.ld = std::max(m.r, 1);
             o.p = (cplx<G>*)cx.tmp_alloc(sizeof(cplx<G>) * (size_t)o.ld * std::max(m.c, 1));
-            std::vector<CopyDesc<G, T>> cd{{m.r, m.c, m.ld, o.ld, m.p, o.p, 0}};
-            if (m.r > 0 && m.c > 0) copy_batched<G, T>(cx.pool, cd);
+            if (m.r > 0 && m.c > 0) {
+              cvt.push_back({m.r, m.c, m.ld, o.ld, m.p, o.p, 0});
+              done[m.p] = o;
+            }
           }
           return o;
-        };
-        // the parents' weights T in the Gram precision (one copy per parent)
-        std::map<std::pair<int, int>, Mat<G>> tconv;
-        auto convT = [&](const Mat<T>& m, int p, int key) -> Mat<G> {
-          if constexpr (std::is_same<G, T>::value) {
-            (void)p;
-            (void)key;
-            return m;
-          } else {
-            auto it = tconv.find({p, key});
-            if (it != tconv.end()) return it->second;
-            Mat<G> o;
-            o.r = m.r;
-            o.c = m.c;
-            o.ld = std::max(m.r, 1);
-            o.p = (cplx<G>*)cx.tmp_alloc(sizeof(cplx<G>) * (size_t)o.ld * std::max(m.c, 1));
-            std::vector<CopyDesc<G, T>> cd{{m.r, m.c, m.ld, o.ld, m.p, o.p, 0}};
-            if (m.r > 0 && m.c > 0) copy_batched<G, T>(cx.pool, cd);
-            tconv[{p, key}] = o;
-            return o;
-          }
         };
         std::vector<Mat<G>> GU(nodes.size()), GV(nodes.size()), XU(nodes.size()),
             XV(nodes.size());
@@ -754,7 +745,7 @@ void build_2d(Ctx& cx, const std::vector<Tree1>& tx, const std::vector<Tree1>& t
             const Node2<T>& par = bd.node(p, l - 1, z >> 2);
             Mat<G> r = conv(nd.R), w = conv(nd.W);
             if (nd.wU > 0 && par.TU.c > 0) {
-              Mat<G> tu = convT(par.TU, p, 2 * (z >> 2));
+              Mat<G> tu = conv(par.TU);
               // T^U_parent is upper triangular
               gx.push_back({nd.wU, par.TU.c, r.c, r.ld, tu.ld, XU[i].ld, r.p, tu.p, XU[i].p, G(1),
                             G(0), G(0), 0, 0, 2});
@@ -762,7 +753,7 @@ void build_2d(Ctx& cx, const std::vector<Tree1>& tx, const std::vector<Tree1>& t
                                 XU[i].p, GU[i].p, G(1), G(0), G(1), 1});
             }
             if (nd.wV > 0 && par.TV.c > 0) {
-              Mat<G> tv = convT(par.TV, p, 2 * (z >> 2) + 1);
+              Mat<G> tv = conv(par.TV);
               gx.push_back({nd.wV, par.TV.c, w.c, w.ld, tv.ld, XV[i].ld, w.p, tv.p, XV[i].p, G(1),
                             G(0), G(0), 0, 0, 2});
               gnc[3].push_back({nd.wV, nd.wV, XV[i].c, XV[i].ld, XV[i].ld, GV[i].ld, XV[i].p,
@@ -770,6 +761,7 @@ void build_2d(Ctx& cx, const std::vector<Tree1>& tx, const std::vector<Tree1>& t
             }
           }
         }
+        if constexpr (!std::is_same<T, G>::value) copy_batched<G, T>(cx.pool, cvt);
         fill_batched<G>(cx.pool, fz);
         gemm_batched<G>(cx.pool, gx, OpN, OpN);
         for (int s = 0; s < 4; ++s) {
