@@ -275,18 +275,23 @@ __global__ void adj_reduce_kernel(const double2* __restrict__ part, double2* __r
   }
 }
 
-constexpr int64_t ADJ_MIN_ROWS = 2048;   // rows per chunk, at least
-constexpr int64_t ADJ_WG_TARGET = 2048;  // workgroups per problem launch wanted
+constexpr int64_t ADJ_MIN_ROWS = 256;    // rows per chunk, at least
+constexpr int64_t ADJ_WG_TARGET = 1024;  // workgroups per problem launch wanted
 
-// Row chunks of the adjoint apply for a plan: as many as fill the device
-// (about ADJ_WG_TARGET workgroups per problem) but no more than the partial
-// buffer of cap bytes holds; 0 when not even one chunk fits.
+// Row chunks of the adjoint apply for a plan: as many as fill the device with
+// whole rounds (ADJ_WG_TARGET workgroups per problem over its tiles and
+// right-hand sides: two rounds of two workgroups a CU) but no more than the
+// partial buffer of cap bytes holds; 0 when not even one chunk fits.  A chunk
+// costs a pass over its partial vector, about 40 rows' worth of products, so
+// it has at least 256 rows: 96 x 160, M = 23 040, three right-hand sides takes
+// 283 us in 56 chunks, 389 us in the 12 of at least 2048 rows (216
+// workgroups, one wave per SIMD); n = 512 the same in 16 and 32 chunks.
 int adj_chunks(const Plan* P, int nrhs, size_t cap) {
   int64_t want = 1;
   for (const Problem& q : P->probs) {
     const int64_t tiles = (int64_t)ceil_div(q.nx, AT) * ceil_div(q.ny, AT);
     const int64_t by_rows = std::max<int64_t>(1, (q.M + ADJ_MIN_ROWS - 1) / ADJ_MIN_ROWS);
-    want = std::max(want, std::min(by_rows, (ADJ_WG_TARGET + tiles - 1) / tiles));
+    want = std::max(want, std::min(by_rows, ADJ_WG_TARGET / (tiles * nrhs)));
   }
   const size_t per_chunk = sizeof(double2) * (size_t)P->Ntot * (size_t)nrhs;
   const int64_t fit = per_chunk ? (int64_t)(cap / per_chunk) : want;
