@@ -1924,10 +1924,13 @@ __global__ void pchol_finish_kernel(const PcholDesc* __restrict__ descs, const i
 // substitution), R upper triangular of order k <= TRS_B; one workgroup per
 // (system, column of B).  The workgroup stages R's upper triangle in LDS,
 // packed by columns ((r, c), r <= c, at c (c + 1) / 2 + r), with the inverted
-// diagonal; one wave then substitutes with the right-hand side in registers
-// (lane l holds rows l and l + 64) and broadcasts each solved entry with a
-// lane read.
+// diagonal; each wave then substitutes with one right-hand side at a time in
+// registers (lane l holds rows l and l + 64) and broadcasts each solved entry
+// with a lane read.  A workgroup takes TRS_RHS right-hand sides, so the triangle
+// is staged once for all of them (a workgroup per right-hand side staged it 128
+// times for an inversion: 17 ms of the n = 512 factorization).
 constexpr int TRS_B = 128;
+constexpr int TRS_RHS = 32;
 
 template <typename T, bool CT, class DS>
 __global__ __launch_bounds__(256) void trsv_lds_kernel(DS descs) {
@@ -1935,8 +1938,8 @@ __global__ __launch_bounds__(256) void trsv_lds_kernel(DS descs) {
   __shared__ C2 Rp[TRS_B * (TRS_B + 1) / 2];
   __shared__ C2 inv[TRS_B];
   const TrsDesc<T> d = descs[blockIdx.x];
-  const int rhs = blockIdx.y;
-  if (rhs >= d.nrhs || d.k <= 0) return;
+  const int rhs0 = blockIdx.y * TRS_RHS;
+  if (rhs0 >= d.nrhs || d.k <= 0) return;
   const int k = min(d.k, TRS_B);
   const int ne = k * (k + 1) / 2;
   const int tid = threadIdx.x;
@@ -1967,36 +1970,37 @@ __global__ __launch_bounds__(256) void trsv_lds_kernel(DS descs) {
     inv[tid] = mk<T>(r.x / den, -r.y / den);
   }
   __syncthreads();
-  if (tid >= 64) return;
-  const int lane = tid;
-  C2* b = d.B + (int64_t)rhs * d.ldb;
-  C2 x0 = lane < k ? b[lane] : mk<T>(0, 0);
-  C2 x1 = lane + 64 < k ? b[lane + 64] : mk<T>(0, 0);
-  for (int s = 0; s < k; ++s) {
-    const int i = CT ? s : k - 1 - s;
-    const int ow = i & 63;
-    const C2 bi = (i >> 6) ? x1 : x0;
-    C2 xi = cmul(bi, inv[i]);
-    xi.x = lane_bcast(xi.x, ow);
-    xi.y = lane_bcast(xi.y, ow);
-    if (lane == ow) {
-      if (i >> 6) x1 = xi;
-      else x0 = xi;
+  const int lane = tid & 63;
+  for (int rhs = rhs0 + (tid >> 6); rhs < min(d.nrhs, rhs0 + TRS_RHS); rhs += 4) {
+    C2* b = d.B + (int64_t)rhs * d.ldb;
+    C2 x0 = lane < k ? b[lane] : mk<T>(0, 0);
+    C2 x1 = lane + 64 < k ? b[lane + 64] : mk<T>(0, 0);
+    for (int s = 0; s < k; ++s) {
+      const int i = CT ? s : k - 1 - s;
+      const int ow = i & 63;
+      const C2 bi = (i >> 6) ? x1 : x0;
+      C2 xi = cmul(bi, inv[i]);
+      xi.x = lane_bcast(xi.x, ow);
+      xi.y = lane_bcast(xi.y, ow);
+      if (lane == ow) {
+        if (i >> 6) x1 = xi;
+        else x0 = xi;
+      }
+      if (!CT) {
+        // rows above i: b_r -= R(r, i) x_i
+        const int off = i * (i + 1) / 2;
+        if (lane < i) x0 = csub(x0, cmul(Rp[off + lane], xi));
+        if (lane + 64 < i) x1 = csub(x1, cmul(Rp[off + lane + 64], xi));
+      } else {
+        // rows below i: b_r -= conj(R(i, r)) x_i
+        const int r0 = lane, r1 = lane + 64;
+        if (r0 > i && r0 < k) x0 = csub(x0, cmul(cconj(Rp[r0 * (r0 + 1) / 2 + i]), xi));
+        if (r1 > i && r1 < k) x1 = csub(x1, cmul(cconj(Rp[r1 * (r1 + 1) / 2 + i]), xi));
+      }
     }
-    if (!CT) {
-      // rows above i: b_r -= R(r, i) x_i
-      const int off = i * (i + 1) / 2;
-      if (lane < i) x0 = csub(x0, cmul(Rp[off + lane], xi));
-      if (lane + 64 < i) x1 = csub(x1, cmul(Rp[off + lane + 64], xi));
-    } else {
-      // rows below i: b_r -= conj(R(i, r)) x_i
-      const int r0 = lane, r1 = lane + 64;
-      if (r0 > i && r0 < k) x0 = csub(x0, cmul(cconj(Rp[r0 * (r0 + 1) / 2 + i]), xi));
-      if (r1 > i && r1 < k) x1 = csub(x1, cmul(cconj(Rp[r1 * (r1 + 1) / 2 + i]), xi));
-    }
+    if (lane < k) b[lane] = x0;
+    if (lane + 64 < k) b[lane + 64] = x1;
   }
-  if (lane < k) b[lane] = x0;
-  if (lane + 64 < k) b[lane + 64] = x1;
 }
 
 // ------------------------------------------------------------ copy / fill
@@ -2871,12 +2875,11 @@ static void trsv_small(DescPool& pool, const std::vector<TrsDesc<T>>& d, bool ct
   for (auto& q : d) maxr = std::max(maxr, q.nrhs);
   with_descs(pool, d.data(), d.size(), [&](auto dd) {
     using DS = decltype(dd);
+    const dim3 grid((unsigned)d.size(), (unsigned)((maxr + TRS_RHS - 1) / TRS_RHS));
     if (ct)
-      hipLaunchKernelGGL((trsv_lds_kernel<T, true, DS>), dim3((unsigned)d.size(), maxr), dim3(256),
-                         0, pool.stream, dd);
+      hipLaunchKernelGGL((trsv_lds_kernel<T, true, DS>), grid, dim3(256), 0, pool.stream, dd);
     else
-      hipLaunchKernelGGL((trsv_lds_kernel<T, false, DS>), dim3((unsigned)d.size(), maxr),
-                         dim3(256), 0, pool.stream, dd);
+      hipLaunchKernelGGL((trsv_lds_kernel<T, false, DS>), grid, dim3(256), 0, pool.stream, dd);
   });
   ND_HIP(hipGetLastError());
 }
