@@ -1681,6 +1681,90 @@ __global__ __launch_bounds__(WY_NT) void wy_merge_kernel(DS descs) {
   }
 }
 
+// wy_merge for FP32: the half's T in LDS as 32 x 32 blocks (128 KB with S's),
+// joined by doubling: two pairs of panels, then the two pairs, every product a
+// sum of 32 x 32 ones on the FP32 matrix cores, a 16 x 16 tile a wave.  One
+// global round trip in all; staging the operands step by step with the products
+// on the vector units took 51 us a launch.
+constexpr int WYB = QR_HB / QR_NB;   // panels of a half
+template <class DS>
+__global__ __launch_bounds__(1024) void wy_merge_f32_kernel(DS descs) {
+  typedef float2 Blk[QR_NB][QR_NB + 1];
+  __shared__ Blk Tb[WYB * (WYB + 1) / 2], Sb[WYB * (WYB - 1) / 2];
+  const WyDesc<float> d = descs[blockIdx.x];
+  const int kb = d.kb, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nb = (kb + QR_NB - 1) / QR_NB;
+  auto ti = [](int i, int j) { return j * (j + 1) / 2 + i; };    // i <= j
+  auto si = [](int i, int j) { return j * (j - 1) / 2 + i; };    // i < j
+  const int r = tid & 31, c = tid >> 5;
+#pragma unroll
+  for (int j = 0; j < WYB; ++j) {
+    Tb[ti(j, j)][r][c] = j < nb ? ldc(d.Tw + (int64_t)j * QR_NB * QR_NB + r + c * QR_NB)
+                                : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < j; ++i)
+      Sb[si(i, j)][r][c] = QR_NB * i + r < kb && QR_NB * j + c < kb
+                               ? ldc(d.S + QR_NB * i + r + (int64_t)(QR_NB * j + c) * d.lds)
+                               : make_float2(0.f, 0.f);
+  }
+  __syncthreads();
+  // tile (wave % 4) of a block: re, im += A B
+  const int i0 = 16 * ((wave >> 1) & 1), j0 = 16 * (wave & 1);
+  auto mm = [&](const Blk& A, const Blk& B, flt4& re, flt4& im) {
+#pragma unroll
+    for (int s = 0; s < QR_NB / 4; ++s) {
+      const int k = 4 * s + (lane >> 4);
+      const float2 a = A[i0 + (lane & 15)][k], b = B[k][j0 + (lane & 15)];
+      re = mfma16(a.x, b.x, re);
+      im = mfma16(a.x, b.y, im);
+      re = mfma16(-a.y, b.y, re);
+      im = mfma16(a.y, b.x, im);
+    }
+  };
+  auto put = [&](Blk& D, const flt4& re, const flt4& im, float sg) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      D[i0 + mrow<float>(lane, v)][j0 + (lane & 15)] = make_float2(sg * re[v], sg * im[v]);
+  };
+  const flt4 z = {0.f, 0.f, 0.f, 0.f};
+  // pairs (0, 1) and (2, 3): T(p, p + 1) = -T(p, p) S(p, p + 1) T(p + 1, p + 1)
+  {
+    const int p = 2 * (wave >> 2);
+    flt4 re = z, im = z;
+    if (wave < 8) mm(Sb[si(p, p + 1)], Tb[ti(p + 1, p + 1)], re, im);
+    __syncthreads();
+    if (wave < 8) put(Sb[si(p, p + 1)], re, im, 1.f);
+    __syncthreads();
+    re = im = z;
+    if (wave < 8) {
+      mm(Tb[ti(p, p)], Sb[si(p, p + 1)], re, im);
+      put(Tb[ti(p, p + 1)], re, im, -1.f);
+    }
+    __syncthreads();
+  }
+  // the two pairs: block (i, j) of the upper right quarter a wave group
+  {
+    const int i = (wave >> 2) & 1, j = 2 + (wave >> 3);
+    flt4 re = z, im = z;
+    mm(Sb[si(i, 2)], Tb[ti(2, j)], re, im);
+    if (j == 3) mm(Sb[si(i, 3)], Tb[ti(3, 3)], re, im);
+    __syncthreads();
+    put(Sb[si(i, j)], re, im, 1.f);
+    __syncthreads();
+    re = im = z;
+    mm(Tb[ti(i, i)], Sb[si(i, j)], re, im);
+    if (i == 0) mm(Tb[ti(0, 1)], Sb[si(1, j)], re, im);
+    put(Tb[ti(i, j)], re, im, -1.f);
+  }
+  __syncthreads();
+  for (int j = 0; j < nb; ++j)
+    for (int i = 0; i < nb; ++i) {
+      const int gr = QR_NB * i + r, gc = QR_NB * j + c;
+      if (gr < kb && gc < kb)
+        stc(d.Tout + gr + (int64_t)gc * d.ldt, i <= j ? Tb[ti(i, j)][r][c] : make_float2(0.f, 0.f));
+    }
+}
+
 // The end of a factorization, over all of R (kmin x n): for column c < kmin
 // of the block starting at J0, the rows above J0 move from A to R (A keeps
 // zeros there) and R below the diagonal block of c's panel is zero (the
@@ -2659,8 +2743,12 @@ void geqrf_batched(DescPool& pool, const std::vector<QRDesc<T>>& din, void* ws, 
       gemm_batched<T>(pool, g1, OpC, OpN);
       if (!wy.empty()) {
         with_descs(pool, wy.data(), wy.size(), [&](auto dw) {
-          hipLaunchKernelGGL((wy_merge_kernel<T, decltype(dw)>), dim3((unsigned)wy.size()),
-                             dim3(WY_NT), 0, pool.stream, dw);
+          if constexpr (std::is_same<T, float>::value)
+            hipLaunchKernelGGL((wy_merge_f32_kernel<decltype(dw)>), dim3((unsigned)wy.size()),
+                               dim3(1024), 0, pool.stream, dw);
+          else
+            hipLaunchKernelGGL((wy_merge_kernel<T, decltype(dw)>), dim3((unsigned)wy.size()),
+                               dim3(WY_NT), 0, pool.stream, dw);
         });
         ND_HIP(hipGetLastError());
       }
