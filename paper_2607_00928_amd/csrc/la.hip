@@ -1797,7 +1797,8 @@ __global__ void qr_finish_kernel(const QRDesc<T>* __restrict__ descs) {
 // ------------------------------------------------------------ pivoted Cholesky
 constexpr int PC_NB = 128;   // pivots per panel (one Schur update of the Gram per panel)
 
-__global__ void pchol_init_kernel(const PcholDesc* __restrict__ descs, double* trace_out) {
+__global__ void pchol_init_kernel(const PcholDesc* __restrict__ descs, double* trace_out,
+                                  int* state) {
   const PcholDesc d = descs[blockIdx.x];
   __shared__ double red[4];
   double s = 0;
@@ -1811,18 +1812,20 @@ __global__ void pchol_init_kernel(const PcholDesc* __restrict__ descs, double* t
   __syncthreads();
   if (threadIdx.x == 0) {
     trace_out[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    state[blockIdx.x] = 1;
     *d.rank = 0;
   }
 }
 
-// Column-parallel pivoted Cholesky: one launch per pivot column, workgroup w
-// of Gram b owning rows [256 w, 256 w + 256) (one per thread).  The
+// Column-parallel pivoted Cholesky of large Grams: one launch per pivot column,
+// workgroup w of Gram b owning rows [256 w, 256 w + 256) (one per thread).  The
 // workgroups exchange their partials of the Schur diagonal (largest entry,
 // its row, positive trace) through global slots, double-buffered by column
 // parity; the launch boundary orders a column's partials before their use,
 // so no workgroup waits on another inside a launch.  Ties go to the lower
 // row.  state[b]: 1 = still running.
 constexpr int PC_ROWS = 256;
+constexpr int PC_WG_ROWS = 1536;
 
 __device__ inline bool pc_better(double v, int i, double bv, int bi) {
   return v > bv || (v == bv && i >= 0 && (bi < 0 || i < bi));
@@ -1993,6 +1996,158 @@ __global__ __launch_bounds__(256) void pchol_col_kernel(const PcholDesc* __restr
   }
   // partials of the next column
   pc_partial(d, i, di, part + (((size_t)b * 2 + ((k + 1) & 1)) * gsize + w) * 3);
+}
+
+// Panel of pivots k0 .. k0 + panel - 1 of every running Gram of order <= 1024 RPT
+// by one workgroup, thread t owning rows RPT t .. (their diagonal stays in
+// registers): the pivot search needs no exchange between workgroups, so a
+// column costs two barriers and a round trip to memory for the pivot's column
+// instead of a launch (order 256: 2.9 us a column, 10 us as a launch with the
+// gap before it).  The rows' earlier entries of the panel come from L2, the
+// first ones before the pivot is known.
+constexpr int PC_PANEL = 64;   // longest panel
+
+// barrier that orders LDS alone: loads and stores of memory stay in flight
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ inline double warp_max(double v) {
+  v = fmax(v, dpp_get<0x121, 0xF>(v));
+  v = fmax(v, dpp_get<0x122, 0xF>(v));
+  v = fmax(v, dpp_get<0x124, 0xF>(v));
+  v = fmax(v, dpp_get<0x128, 0xF>(v));
+  v = fmax(v, dpp_get<0x142, 0xA>(v));
+  v = fmax(v, dpp_get<0x143, 0xC>(v));
+  return lane_bcast(v, 63);
+}
+
+template <int RPT>
+__global__ __launch_bounds__(1024) void pchol_panel_kernel(const PcholDesc* __restrict__ descs,
+                                                           const double* __restrict__ trace,
+                                                           int* __restrict__ state, int k0,
+                                                           int panel) {
+  constexpr int AHEAD = 16 / RPT;   // earlier entries of a row loaded ahead
+  __shared__ double2 lp[PC_PANEL];
+  __shared__ double rv[2][16], rs[2][16];
+  __shared__ int ri[2][16];
+  const int b = blockIdx.x;
+  if (!state[b]) return;
+  const PcholDesc d = descs[b];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const double tol = d.tol2 * trace[b], none = -1.0 / 0.0;
+  const int i0 = RPT * tid;
+  double di[RPT];
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) di[r] = i0 + r < d.w ? d.d[i0 + r] : none;
+  const double2* Lk = d.L + (int64_t)k0 * d.ldl;
+  for (int kk = 0; kk < panel; ++kk) {
+    const int k = k0 + kk, par = kk & 1;
+    // largest entry of the diagonal, its row (ties to the lower one), positive trace
+    double best = -1.0, sum = 0.0;
+    int bi = -1;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      sum += di[r] > 0 ? di[r] : 0.0;
+      if (di[r] > best) {
+        best = di[r];
+        bi = i0 + r;
+      }
+    }
+    double2 la[RPT][AHEAD];
+    if (kk > 0)
+#pragma unroll
+      for (int r = 0; r < RPT; ++r)
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+          la[r][u] = i0 + r < d.w ? (Lk + (int64_t)min(u, kk - 1) * d.ldl)[i0 + r]
+                                  : mk<double>(0.0, 0.0);
+    {
+      const double m = warp_max(best), s = warp_sum(sum);
+      const uint64_t at = __ballot(bi >= 0 && best == m);
+      const int row = at ? __builtin_amdgcn_readlane(bi, __ffsll((unsigned long long)at) - 1) : -1;
+      if (lane == 0) {
+        rv[par][wave] = m;
+        rs[par][wave] = s;
+        ri[par][wave] = row;
+      }
+    }
+    __syncthreads();   // the last column of L too
+    double bb = lane < nw ? rv[par][lane] : -1.0, ss = lane < nw ? rs[par][lane] : 0.0;
+    const int wi = lane < nw ? ri[par][lane] : -1;
+    const double wv = bb;
+    bb = fmax(bb, dpp_get<0x121, 0xF>(bb));
+    ss += dpp_get<0x121, 0xF>(ss);
+    bb = fmax(bb, dpp_get<0x122, 0xF>(bb));
+    ss += dpp_get<0x122, 0xF>(ss);
+    bb = fmax(bb, dpp_get<0x124, 0xF>(bb));
+    ss += dpp_get<0x124, 0xF>(ss);
+    bb = fmax(bb, dpp_get<0x128, 0xF>(bb));
+    ss += dpp_get<0x128, 0xF>(ss);
+    bb = lane_bcast(bb, 0);
+    ss = lane_bcast(ss, 0);
+    const uint64_t at = __ballot(wi >= 0 && wv == bb);
+    const int p = at ? __builtin_amdgcn_readlane(wi, __ffsll((unsigned long long)at) - 1) : -1;
+    // the same values in every thread
+    if (k >= d.rmax || k >= d.w || ss <= tol || p < 0 || bb <= 0.0) {
+      if (tid == 0) {
+        *d.rank = k;
+        state[b] = 0;
+      }
+      return;
+    }
+    if (tid == 0) d.piv[k] = p;
+    // the pivot row's earlier entries in this panel
+    if (tid < PC_PANEL)
+      lp[tid] = tid < kk ? Lk[p + (int64_t)tid * d.ldl] : mk<double>(0.0, 0.0);
+    double2 v[RPT];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      const int i = i0 + r;   // K holds its lower triangle
+      v[r] = i >= d.w ? mk<double>(0.0, 0.0)
+             : i >= p ? d.K[i + (int64_t)p * d.ldk] : cconj(d.K[p + (int64_t)i * d.ldk]);
+    }
+    const double sdp = sqrt(bb), inv = 1.0 / sdp;
+    lds_barrier();
+    // L(i,k) = (K(i,p) - sum_q L(i,q) conj(L(p,q))) / sqrt(d_p)
+    for (int q = 0; q < kk; q += AHEAD) {
+      if (q > 0)
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+#pragma unroll
+          for (int u = 0; u < AHEAD; ++u)
+            la[r][u] = i0 + r < d.w ? (Lk + (int64_t)min(q + u, kk - 1) * d.ldl)[i0 + r]
+                                    : mk<double>(0.0, 0.0);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const double2 c = lp[q + u];
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) v[r] = csub(v[r], cmulc(c, la[r][u]));
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      const int i = i0 + r;
+      if (i >= d.w) continue;
+      // v / sdp: the product with 1 / sdp and one correction
+      double qx = v[r].x * inv, qy = v[r].y * inv;
+      qx = fma(fma(-qx, sdp, v[r].x), inv, qx);
+      qy = fma(fma(-qy, sdp, v[r].y), inv, qy);
+      if (di[r] <= -1e300) qx = qy = 0.0;
+      if (i == p) {
+        qx = sdp;
+        qy = 0.0;
+      }
+      d.L[i + (int64_t)k * d.ldl] = mk<double>(qx, qy);
+      if (i == p) di[r] = none;
+      else if (di[r] > -1e300) di[r] -= qx * qx + qy * qy;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < RPT; ++r)
+    if (i0 + r < d.w) d.d[i0 + r] = di[r];
 }
 
 __global__ void pchol_finish_kernel(const PcholDesc* __restrict__ descs, const int* state, int kend) {
@@ -2908,47 +3063,62 @@ void pchol_batched(DescPool& pool, const std::vector<PcholDesc>& d) {
   }
   const int nb = (int)d.size();
   auto* dd = (PcholDesc*)pool.push(d.data(), sizeof(PcholDesc) * nb);
-  std::vector<int> ones(nb, 1);
-  std::vector<double> zeros(nb, 0.0);
-  double* trace = (double*)pool.push(zeros.data(), sizeof(double) * nb);
-  int* state = (int*)pool.push(ones.data(), sizeof(int) * nb);
-  hipLaunchKernelGGL(pchol_init_kernel, dim3(nb), dim3(256), 0, pool.stream, dd, trace);
-  int rmax = 0;
-  for (auto& q : d) rmax = std::max(rmax, std::min(q.rmax, q.w));
-  std::vector<GemmDesc<double>> g;
-  std::vector<int> hstate(nb);
-  int maxw = 1;
-  for (auto& q : d) maxw = std::max(maxw, q.w);
+  double* trace = (double*)pool.reserve(sizeof(double) * nb);
+  int* state = (int*)pool.reserve(sizeof(int) * nb);
+  hipLaunchKernelGGL(pchol_init_kernel, dim3(nb), dim3(256), 0, pool.stream, dd, trace, state);
+  int rmax = 0, maxw = 1;
+  for (auto& q : d) {
+    rmax = std::max(rmax, std::min(q.rmax, q.w));
+    maxw = std::max(maxw, q.w);
+  }
+  // One workgroup per Gram up to PC_WG_ROWS rows; from there its reads of the
+  // panel's earlier columns cost as much as a launch per column over many
+  // workgroups (8 Grams, us a column: order 825 6.8 / 10.0, 1233 10.1 / 11.7,
+  // 1600 12.6 / 12.6, 2040 20.6 / 16.2).  Panels of 64 where the Schur updates of
+  // the batch weigh more than those reads (128 Grams of order 1000: 43 us a
+  // column with panels of 32, 33 with 64; 8 of order 825: 6.8, 7.8).
+  const bool wg = maxw <= PC_WG_ROWS;
+  const int panel = !wg ? PC_NB : (int64_t)nb * maxw >= 65536 ? PC_PANEL : PC_PANEL / 2;
   const int gsize = (maxw + PC_ROWS - 1) / PC_ROWS;
   const int64_t grid = (int64_t)nb * gsize;
-  ND_CHECK(grid < (int64_t(1) << 31), NUDFT2_E_INTERNAL, "too many Gram rows for one launch");
-  std::vector<double> pz((size_t)nb * 2 * gsize * 3, 0.0);
-  double* part = (double*)pool.push(pz.data(), sizeof(double) * pz.size());
-  hipLaunchKernelGGL(pchol_part_kernel, dim3((unsigned)grid), dim3(PC_ROWS), 0, pool.stream, dd,
-                     gsize, part, 0);
-  ND_HIP(hipGetLastError());
-  for (int k0 = 0; k0 < rmax; k0 += PC_NB) {
-    const int kb = std::min(PC_NB, rmax - k0);
-    for (int kk = 0; kk < kb; ++kk)
-      hipLaunchKernelGGL(pchol_col_kernel, dim3((unsigned)grid), dim3(PC_ROWS), 0, pool.stream, dd,
-                         trace, state, gsize, part, k0, kk);
+  double* part = nullptr;
+  if (!wg) {
+    ND_CHECK(grid < (int64_t(1) << 31), NUDFT2_E_INTERNAL, "too many Gram rows for one launch");
+    part = (double*)pool.reserve(sizeof(double) * (size_t)nb * 2 * gsize * 3);
+    hipLaunchKernelGGL(pchol_part_kernel, dim3((unsigned)grid), dim3(PC_ROWS), 0, pool.stream, dd,
+                       gsize, part, 0);
     ND_HIP(hipGetLastError());
+  }
+  std::vector<GemmDesc<double>> g;
+  std::vector<int> hstate(nb);
+  for (int k0 = 0; k0 < rmax; k0 += panel) {
+    if (wg) {
+      if (maxw <= 1024)
+        hipLaunchKernelGGL(pchol_panel_kernel<1>, dim3(nb), dim3((maxw + 63) / 64 * 64), 0,
+                           pool.stream, dd, trace, state, k0, panel);
+      else
+        hipLaunchKernelGGL(pchol_panel_kernel<2>, dim3(nb), dim3((maxw + 127) / 128 * 64), 0,
+                           pool.stream, dd, trace, state, k0, panel);
+    } else {
+      const int kb = std::min(PC_NB, rmax - k0);
+      for (int kk = 0; kk < kb; ++kk)
+        hipLaunchKernelGGL(pchol_col_kernel, dim3((unsigned)grid), dim3(PC_ROWS), 0, pool.stream,
+                           dd, trace, state, gsize, part, k0, kk);
+    }
+    ND_HIP(hipGetLastError());
+    if (k0 + panel >= rmax) break;
     // Schur update with this panel's columns for the problems still running
     ND_HIP(hipMemcpyAsync(hstate.data(), state, sizeof(int) * nb, hipMemcpyDeviceToHost,
                           pool.stream));
     ND_HIP(hipStreamSynchronize(pool.stream));
     g.clear();
-    bool any = false;
     for (int i = 0; i < nb; ++i) {
-      if (!hstate[i]) continue;
-      any = true;
       const PcholDesc& q = d[i];
-      int kb = std::min(PC_NB, std::min(q.rmax, q.w) - k0);
-      if (kb <= 0) continue;
+      if (!hstate[i] || std::min(q.rmax, q.w) - k0 <= panel) continue;   // ended, or full
       const double2* Lp = q.L + (int64_t)k0 * q.ldl;
-      g.push_back({q.w, q.w, kb, q.ldl, q.ldl, q.ldk, Lp, Lp, q.K, -1.0, 0.0, 1.0, 1});
+      g.push_back({q.w, q.w, panel, q.ldl, q.ldl, q.ldk, Lp, Lp, q.K, -1.0, 0.0, 1.0, 1});
     }
-    if (!any) break;
+    if (g.empty()) break;
     gemm_batched<double>(pool, g, OpN, OpC);
   }
   int kend = rmax;

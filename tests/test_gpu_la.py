@@ -330,6 +330,60 @@ def test_pchol_trace_rule():
             assert r <= 2 * ropt + 8
 
 
+@pytest.mark.parametrize("sizes", [
+    # one workgroup per Gram: waves, panels of 32 and rmax at and around their
+    # ends, ranks of zero, one row per thread (<= 1024) and two
+    [(1, 1, 1), (2, 2, 2), (31, 31, 31), (32, 32, 32), (33, 33, 33), (64, 64, 64), (65, 65, 40),
+     (100, 32, 60), (100, 33, 60), (100, 64, 64), (0, 0, 0), (90, 0, 40), (50, 50, 0)],
+    [(1024, 96, 70), (200, 200, 65), (7, 7, 7)],
+    [(1025, 64, 64), (1023, 97, 96), (1536, 40, 33), (5, 5, 3)],
+    # panels of 64 (Grams x order >= 65536)
+    [(1030, 129, 128), (1030, 140, 65), (64, 64, 64)] + [(3, 2, 2)] * 61,
+    # a column per launch over several workgroups
+    [(1537, 140, 131), (64, 64, 64), (300, 300, 128)],
+])
+def test_pchol_greedy(sizes):
+    # K of exact rank r with well separated pivots: the greedy order is the
+    # oracle's, and L agrees to FP64 rounding (about w kappa eps, kappa <= 1e4)
+    rng = np.random.default_rng(23)
+    keep, data, ptr = [], [], []
+    tol2 = 1e-11
+    for (n, rm, rk) in sizes:
+        F = crandn(rng, n, rk) * (2.0 ** (-10.0 * np.arange(n) / max(n, 1)))[rng.permutation(n), None] \
+            if n and rk else np.zeros((n, rk))
+        K = F @ F.conj().T
+        tK = to_dev(K, 0) if n else torch.zeros(1, dtype=torch.complex128, device=DEV)
+        tL = torch.zeros((max(rm, 1), max(n, 1)), dtype=torch.complex128, device=DEV)
+        keep += [tK, tL]
+        data.append((K, tL, n, rm, rk))
+        ptr += [tK.data_ptr(), tL.data_ptr()]
+    rmax = [s[1] for s in sizes]
+    a1, p1 = i32([s[0] for s in sizes])
+    a2, p2 = i32(rmax)
+    a3, p3 = i64(ptr)
+    ranks = np.zeros(len(sizes), np.int32)
+    piv = np.zeros(sum(rmax), np.int32)
+    st = lib.nudft2_test_pchol(len(sizes), p1, p2, p3, tol2,
+                               ranks.ctypes.data_as(C.POINTER(C.c_int32)),
+                               piv.ctypes.data_as(C.POINTER(C.c_int32)))
+    assert st == 0, lib.nudft2_last_error()
+    off = 0
+    for (K, tL, n, rm, rk), r in zip(data, ranks):
+        S, want = K.copy(), []
+        Lw = np.zeros((n, min(rm, rk)), complex)
+        for k in range(min(rm, rk)):
+            p = int(np.argmax(np.where(np.isin(np.arange(n), want), -1.0, S.diagonal().real)))
+            Lw[:, k] = S[:, p] / np.sqrt(S[p, p].real)
+            S = S - np.outer(Lw[:, k], Lw[:, k].conj())
+            want.append(p)
+        assert r == min(rm, rk), (n, rm, rk, r)
+        assert piv[off:off + r].tolist() == want, (n, rm, rk)
+        off += rm
+        if r:
+            L = tL.cpu().numpy().T[:n, :r]
+            assert np.abs(L - Lw).max() <= 1e-9 * np.abs(Lw).max(), (n, rm, rk)
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("ct", [0, 1])
 def test_trsv(prec, ct):
