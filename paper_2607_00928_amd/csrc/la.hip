@@ -1095,6 +1095,142 @@ __global__ __launch_bounds__(256) void gemm_skinny_c16_kernel(DS descs, int spli
   }
 }
 
+// Products with 3 or 5 to 16 columns, B not transposed (sweeps with several
+// right-hand sides): bound by latency, then by the read of A.  A workgroup
+// takes 16 RT rows of C; its four waves take every fourth chunk of 16 k, each
+// with up to four chunks (8 to 16 KB of A) in flight, straight from memory in
+// the matrix instructions' layout (lane group g of a chunk holds k = 4 g ..
+// 4 g + 3: op C reads 4 consecutive k of a column, op N 16 rows of one), and
+// their sums meet in LDS.  4 products 256 x 16 x 256: 7.8 us; the 64 x 64
+// tiles, a quarter of their columns used and 16 workgroups in the launch, took
+// 19.4.  With `part`, k range z of splits stores its tile at
+// part[((y splits + z) gridDim.x + x) 256 RT] for gemm_n16_reduce_kernel.
+// Elements 0, 1, 8, 9: 16-byte loads for float2, which global memory takes at
+// any element's alignment
+typedef float gf4u __attribute__((ext_vector_type(4), aligned(8)));
+__device__ __forceinline__ void ldc4(const float2* p, float2 (&o)[4]) {
+  const gf4u u = *(const __attribute__((address_space(1))) gf4u*)p;
+  const gf4u w = *(const __attribute__((address_space(1))) gf4u*)(p + 8);
+  o[0] = make_float2(u.x, u.y);
+  o[1] = make_float2(u.z, u.w);
+  o[2] = make_float2(w.x, w.y);
+  o[3] = make_float2(w.z, w.w);
+}
+__device__ __forceinline__ void ldc4(const double2* p, double2 (&o)[4]) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) o[s] = ldc(p + (s & 1) + 8 * (s >> 1));
+}
+template <typename T, int OPA, int RT, class DS>
+__global__ __launch_bounds__(256) void gemm_n16_kernel(DS descs, int splits, cplx<T>* part) {
+  using C2 = cplx<T>;
+  using V4 = std::conditional_t<sizeof(T) == 4, flt4, dbl4>;
+  constexpr int UC = 4;
+  __shared__ C2 red[4][RT][16][17];
+  const GemmDesc<T> d = descs[blockIdx.y];
+  const int i0 = blockIdx.x * 16 * RT;
+  if (i0 >= d.m || d.n <= 0) return;
+  const int kc = ((d.k + splits - 1) / splits + 15) / 16 * 16;
+  int kb = blockIdx.z * kc, ke = min(d.k, kb + kc);
+  if (kb >= ke && splits > 1) return;
+  // nonzeros of A in rows i0 .. i0 + 16 RT - 1 (see GemmDesc::tri)
+  if (d.tri == (OPA == OpN ? 1 : 2)) ke = min(ke, i0 + 16 * RT);
+  else if (d.tri != 0) kb = max(kb, i0);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, g = lane >> 4;
+  const C2* Ap[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int64_t i = min(i0 + 16 * r + lo, d.m - 1);
+    Ap[r] = d.A + (OPA == OpN ? i : i * d.lda);
+  }
+  const C2* Bp = d.B + (int64_t)min(lo, d.n - 1) * d.ldb;
+  V4 re[RT], im[RT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) re[r] = im[r] = V4{0, 0, 0, 0};
+  for (int k0 = kb + 16 * wave; k0 < ke; k0 += 64 * UC) {
+    C2 a[UC][RT][4], b[UC][4];
+#pragma unroll
+    for (int u = 0; u < UC; ++u) {
+      const int k = k0 + 64 * u + 2 * g;
+      if (k0 + 64 * u + 16 <= ke) {
+        ldc4(Bp + k, b[u]);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          if constexpr (OPA == OpN) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) a[u][r][s] = ldc(Ap[r] + (int64_t)(k + (s & 1) + 8 * (s >> 1)) * d.lda);
+          } else {
+            ldc4(Ap[r] + k, a[u][r]);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int64_t kk = k + (s & 1) + 8 * (s >> 1);
+          const bool on = kk < ke;
+          b[u][s] = on ? ldc(Bp + kk) : mk<T>(0, 0);
+#pragma unroll
+          for (int r = 0; r < RT; ++r)
+            a[u][r][s] = on ? ldc(Ap[r] + (OPA == OpN ? kk * d.lda : kk)) : mk<T>(0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UC; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          const C2 x = a[u][r][s], y = b[u][s];
+          const T xi = OPA == OpN ? x.y : -x.y;
+          re[r] = mfma16(x.x, y.x, re[r]);
+          im[r] = mfma16(x.x, y.y, im[r]);
+          re[r] = mfma16(-xi, y.y, re[r]);
+          im[r] = mfma16(xi, y.x, im[r]);
+        }
+  }
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      red[wave][r][lo][mrow<T>(lane, v)] = mk<T>(re[r][v], im[r][v]);
+  __syncthreads();
+  const int i = tid & 15, j = tid >> 4;
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const C2 v = cadd(cadd(red[0][r][j][i], red[1][r][j][i]), cadd(red[2][r][j][i], red[3][r][j][i]));
+    if (part)
+      part[(((size_t)blockIdx.y * splits + blockIdx.z) * gridDim.x + blockIdx.x) * (256 * RT) +
+           256 * r + tid] = v;
+    else if (i0 + 16 * r + i < d.m && j < d.n)
+      skinny_store(d, i0 + 16 * r + i, j, v, 1);
+  }
+}
+
+// Sum of gemm_n16_kernel's partial tiles, in the order of their k ranges
+template <typename T, int RT, class DS>
+__global__ __launch_bounds__(256) void gemm_n16_reduce_kernel(DS descs, int splits,
+                                                              const cplx<T>* __restrict__ part) {
+  const GemmDesc<T> d = descs[blockIdx.y];
+  const int i = blockIdx.x * 16 + (threadIdx.x & 15), j = threadIdx.x >> 4;
+  if (i >= d.m || j >= d.n) return;
+  const int kc = ((d.k + splits - 1) / splits + 15) / 16 * 16;
+  const int nz = kc > 0 ? min(splits, (d.k + kc - 1) / kc) : 0, tiles = gridDim.x / RT;
+  const cplx<T>* p = part + ((size_t)blockIdx.y * splits * tiles + blockIdx.x / RT) * (256 * RT) +
+                     256 * (blockIdx.x % RT) + threadIdx.x;
+  const size_t zs = (size_t)tiles * (256 * RT);
+  cplx<T> v = mk<T>(0, 0);
+  int z = 0;
+  for (; z + 8 <= nz; z += 8) {
+    cplx<T> t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = p[(z + u) * zs];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v = cadd(v, t[u]);
+  }
+  for (; z < nz; ++z) v = cadd(v, p[z * zs]);
+  skinny_store(d, i, j, v, 1);
+}
+
 // Small products with a long k: C (m x n, m, n <= 16 MB, 16 NB) += alpha
 // A^H B (the Grams of tall panels).  Memory-bound on A and B: workgroup x
 // takes kc rows of k (chosen per launch for about 2048 workgroups), each wave
@@ -2509,6 +2645,58 @@ static int device_cus() {
   return cus;
 }
 
+// Products with at most 16 columns on gemm_n16_kernel; false where the k
+// ranges' sums have no scratch (the caller's tiles add them atomically).
+template <typename T>
+static bool n16_batched(DescPool& pool, const std::vector<GemmDesc<T>>& sub, Op opA, int maxm,
+                        int maxn, int maxk) {
+  const int n = (int)sub.size();
+  // 32 rows a workgroup (B read half as often) where that still fills the device
+  const int t16 = (maxm + 15) / 16;
+  const bool two = (int64_t)t16 * n >= 4096;
+  const int rt = two ? 2 : 1, gx = (t16 + rt - 1) / rt;
+  // k ranges of 256 or more, to about four workgroups a CU
+  const int64_t wgs = (int64_t)gx * n, slots = 4 * (int64_t)device_cus();
+  const size_t tile_b = (size_t)256 * rt * sizeof(cplx<T>);
+  int splits = 1;
+  cplx<T>* part = nullptr;
+  if (maxk >= 1024 && wgs <= slots / 2) {
+    const int64_t sp = std::min<int64_t>({(slots + wgs - 1) / wgs, maxk / 256,
+                                          (int64_t)(kGemmPartBytes / (tile_b * (size_t)wgs))});
+    if (sp >= 2) {
+      part = (cplx<T>*)pool.stream_scratch(kGemmPartBytes);
+      if (!part) return false;
+      splits = (int)sp;
+    }
+  }
+  double fl = 0;
+  for (auto& g : sub) fl += gemm_flops(g, opA, OpN);
+  with_descs(pool, sub.data(), sub.size(), [&](auto dd) {
+    using DS = decltype(dd);
+    ProfScope ps(pool.stream, sizeof(T) == 4 ? KC_GEMM32 : KC_GEMM64, fl, n, maxm, maxn, maxk,
+                 (int)opA * 2 + 10 * splits + 2000, true);
+    hipEvent_t e1 = part ? nullptr : ps.stop();
+    const dim3 grid((unsigned)gx, (unsigned)n, (unsigned)splits);
+    auto launch = [&](auto op, auto r) {
+      constexpr int OPA = decltype(op)::value, RT = decltype(r)::value;
+      hipExtLaunchKernelGGL((gemm_n16_kernel<T, OPA, RT, DS>), grid, dim3(256), 0, pool.stream,
+                            ps.start(), e1, 0, dd, splits, part);
+      if (part)
+        hipExtLaunchKernelGGL((gemm_n16_reduce_kernel<T, RT, DS>),
+                              dim3((unsigned)(gx * RT), (unsigned)n), dim3(256), 0, pool.stream,
+                              nullptr, ps.stop(), 0, dd, splits, part);
+    };
+    auto rows = [&](auto op) {
+      if (two) launch(op, std::integral_constant<int, 2>{});
+      else launch(op, std::integral_constant<int, 1>{});
+    };
+    if (opA == OpN) rows(std::integral_constant<int, (int)OpN>{});
+    else rows(std::integral_constant<int, (int)OpC>{});
+  });
+  ND_HIP(hipGetLastError());
+  return true;
+}
+
 template <typename T>
 void gemm_batched(DescPool& pool, const std::vector<GemmDesc<T>>& d, Op opA, Op opB,
                   int splits_force) {
@@ -2585,6 +2773,16 @@ void gemm_batched(DescPool& pool, const std::vector<GemmDesc<T>>& d, Op opA, Op 
       smallmn_batched<T>(pool, sub, maxm, maxn, maxk);
       continue;
     }
+    // Columns from which gemm_n16_kernel beats the one-column-at-a-time kernels
+    // below (us: op N 9001 x 3 x 256 11 / 21, FP64 17 / 24, but 512 x 240^2 x 3 184
+    // / 146 in FP64; op C 16 x 564^2 FP32 with 4 columns 20 / 18, 5 19 / 26)
+    // and the sizes: op N over many row tiles needs a k that keeps the four waves
+    // busy (1408 products 167 x 8 x 95: 137 / 74 us, 64 of 281 x 8 x 238: 22 / 73)
+    const int n16 = sizeof(T) == 4 && opA == OpN ? 3 : 5;
+    const bool k16 = opA == OpC || maxk >= 192 || (int64_t)ceil_div(maxm, 16) * (int64_t)n <= 512;
+    if (splits_force == 0 && maxn >= n16 && maxn <= 16 && opB == OpN && k16 && !lower_any &&
+        n16_batched<T>(pool, sub, opA, maxm, maxn, maxk))
+      continue;
     if (maxn <= SK_N && opB == OpN) {
       skinny_batched<T>(pool, sub, opA, maxm, maxn, maxk, force);
       continue;

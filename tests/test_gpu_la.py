@@ -152,6 +152,50 @@ def test_gemm_skinny(prec, opa, beta):
         assert np.abs(got - ref).max() < TOL[prec] * scale * max(1, k) ** 0.5 * 10, (m, n, k)
 
 
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("opa", [0, 1])
+@pytest.mark.parametrize("shapes", [
+    # tiles of 16 rows, chunks of 16 k and rounds of 256 at and past their ends
+    [(1, 9, 1), (16, 16, 16), (17, 16, 15), (33, 9, 65), (256, 16, 256), (100, 13, 1023), (5, 1, 300),
+     (48, 16, 257), (40, 12, 0)],
+    # k ranges summed through scratch (maxk >= 1024), a product with fewer of them
+    [(256, 16, 9001), (31, 10, 1024), (16, 12, 300)],
+    # 32 rows a workgroup
+    [(65521, 9, 200)],
+])
+def test_gemm_up_to_16_columns(prec, opa, shapes):
+    """Entrywise against the FP64 product (FP64: of the oracle's rounding),
+    relative to |op(A)| |B|: a few roundings times sqrt(k); leading dimensions
+    that leave columns aligned to single elements only."""
+    rng = np.random.default_rng(500 + 4 * prec + opa)
+    ct = np.complex64 if prec else np.complex128
+    alpha, beta = 0.8 - 0.5j, 0.5
+    mats, keep, mnk, ld, ptr = [], [], [], [], []
+    for (m, n, k) in shapes:
+        A = crandn(rng, *((m, k) if opa == 0 else (k, m))).astype(ct)
+        B, Cm = crandn(rng, k, n).astype(ct), crandn(rng, m, n).astype(ct)
+        pads = [np.concatenate([X, np.zeros((1, X.shape[1]), ct)]) for X in (A, B, Cm)]
+        ts = [to_dev(X, prec) if X.size else torch.zeros(1, dtype=torch.complex128, device=DEV)
+              for X in pads]
+        keep += ts
+        mats.append((A, B, Cm, ts[2]))
+        mnk += [m, n, k]
+        ld += [X.shape[0] for X in pads]
+        ptr += [t.data_ptr() for t in ts]
+    a1, p1 = i32(mnk)
+    a2, p2 = i32(ld)
+    a3, p3 = i64(ptr)
+    st = lib.nudft2_test_gemm(prec, opa, 0, len(shapes), p1, p2, p3, alpha.real, alpha.imag, beta)
+    assert st == 0, lib.nudft2_last_error()
+    eps = 2.0 ** -24 if prec else 2.0 ** -53
+    for (m, n, k), (A, B, Cm, tc) in zip(shapes, mats):
+        oA = (A if opa == 0 else A.conj().T).astype(np.complex128)
+        ref = alpha * (oA @ B.astype(np.complex128)) + beta * Cm.astype(np.complex128)
+        scale = abs(alpha) * (np.abs(oA) @ np.abs(B)) + beta * np.abs(Cm)
+        err = (np.abs(from_dev(tc, m + 1, n)[:m] - ref) / scale).max()
+        assert err < 8 * eps * np.sqrt(max(k, 4)), (m, n, k, err)
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("beta", [0.0, 0.5])
 def test_gemm_skinny_ch_long_k_few_rows(prec, beta):
