@@ -160,7 +160,15 @@ __global__ __launch_bounds__(256, 2) void apply_fwd_kernel(
 
 constexpr int AT = 64;     // output tile (kx, ky)
 constexpr int AK = 16;     // points per stage
+constexpr int AP = 32;     // points per fill of the phase tables
 
+// FP64 instructions and FP64 matrix instructions do not overlap here, so the
+// phases (some 70 instructions each) count in full beside 3072 clk of matrix
+// work a stage: their tables are filled for two stages at a time, each thread
+// the same number of entries (a fill per stage left a quarter of the threads
+// with four of them and the others waiting with two: 96 x 160, M = 23 040, three
+// right-hand sides 294 -> 272 us, 512 x 512, M = 393 216 13.9 -> 13.3 ms; three
+// workgroups a CU with smaller tables are slower, 316 us and 15.1 ms).
 // part[(chunk nrhs + rhs) Ntot + c0 + kx ny + ky] =
 //     sum_{j in chunk} conj(Ax[j][kx]) f_j conj(Ay[j][ky])
 // for the chunk of rows [blockIdx.y rows, (blockIdx.y + 1) rows); every entry
@@ -171,9 +179,8 @@ __global__ __launch_bounds__(256, 2) void apply_adj_kernel(
     int nrhs) {
   __shared__ double Ar[AK][AT + 1], Ai[AK][AT + 1];
   __shared__ double Br[AK][AT + 1], Bi[AK][AT + 1];
-  __shared__ double2 bx[AK][AT / 16], by[AK][AT / 16];
-  __shared__ double2 sx[AK][16], sy[AK][16];
-  __shared__ double2 fv[AK];
+  __shared__ double2 tb[AP][40 + 1];   // a point's phases: 16 of x, 16 of y, 4 bases each
+  __shared__ double2 fv[AP];
 
   const int ntx = (pr.nx + AT - 1) / AT;
   const int kx0 = (blockIdx.x % ntx) * AT;
@@ -196,53 +203,65 @@ __global__ __launch_bounds__(256, 2) void apply_adj_kernel(
       acc3[a][b] = dbl4{0, 0, 0, 0};
     }
 
+  // blocks of 16 x 16 of the sub-tile inside the problem: the matrix
+  // instructions of the others are left to the CU's other workgroup
+  const int na = min(2, (nx - kx0 - wm + 15) / 16), nb = min(2, (ny - ky0 - wn + 15) / 16);
   const int64_t jend = min((int64_t)pr.M, j0 + rows);
-  for (int64_t js = j0; js < jend; js += AK) {
-    __syncthreads();
-    // per-point tables: conj phases (exp(+2 pi i k x)) as conj of expi
+  for (int64_t jt = j0; jt < jend; jt += AP) {
+    // per-point tables: conj phases (exp(+2 pi i k x)) as conj of expi; thread
+    // (point, g) takes entries g, g + 8, ... of the point's 40
     {
-      int p = tid >> 4, t = tid & 15;   // 16 points x 16 entries
-      int64_t j = js + p;
+      const int p = tid & (AP - 1), g = tid / AP;
+      const int64_t j = jt + p;
       double x = 0, y = 0;
-      bool ok = j < jend;
+      const bool ok = j < jend;
       if (ok) { x = pts[2 * (pr.m0 + j)]; y = pts[2 * (pr.m0 + j) + 1]; }
-      sx[p][t] = expi_kx((double)t, x);
-      sy[p][t] = expi_kx((double)t, y);
-      if (t < AT / 16) {
-        bx[p][t] = expi_kx((double)(kx0 + 16 * t - nx / 2), x);
-        by[p][t] = expi_kx((double)(ky0 + 16 * t - ny / 2), y);
+      __syncthreads();   // every wave has read the last points' tables
+      tb[p][g] = expi_kx((double)g, x);
+      tb[p][8 + g] = expi_kx((double)(8 + g), x);
+      tb[p][16 + g] = expi_kx((double)g, y);
+      tb[p][24 + g] = expi_kx((double)(8 + g), y);
+      tb[p][32 + g] = g < 4 ? expi_kx((double)(kx0 + 16 * g - nx / 2), x)
+                            : expi_kx((double)(ky0 + 16 * (g - 4) - ny / 2), y);
+      if (g == 0) fv[p] = ok ? fp[j] : mk<double>(0.0, 0.0);
+    }
+    for (int ps = 0; ps < AP && jt + ps < jend; ps += AK) {
+      __syncthreads();
+      for (int e = tid; e < AK * AT; e += 256) {
+        int p = e / AT, k = e % AT;
+        const double2* t = tb[ps + p];
+        double2 ex = cmul(t[32 + (k >> 4)], t[k & 15]);        // exp(-2 pi i kx x)
+        double2 ey = cmul(t[36 + (k >> 4)], t[16 + (k & 15)]);
+        double2 a = cmulc(ex, fv[ps + p]);                     // conj(ex) f
+        bool okx = kx0 + k < nx, oky = ky0 + k < ny;
+        Ar[p][k] = okx ? a.x : 0.0;
+        Ai[p][k] = okx ? a.y : 0.0;
+        Br[p][k] = oky ? ey.x : 0.0;
+        Bi[p][k] = oky ? -ey.y : 0.0;                          // conj(ey)
       }
-      if (t == 0) fv[p] = ok ? fp[j] : mk<double>(0.0, 0.0);
-    }
-    __syncthreads();
-    for (int e = tid; e < AK * AT; e += 256) {
-      int p = e / AT, k = e % AT;
-      double2 ex = cmul(bx[p][k >> 4], sx[p][k & 15]);   // exp(-2 pi i kx x)
-      double2 ey = cmul(by[p][k >> 4], sy[p][k & 15]);
-      double2 a = cmulc(ex, fv[p]);                        // conj(ex) f
-      bool okx = kx0 + k < nx, oky = ky0 + k < ny;
-      Ar[p][k] = okx ? a.x : 0.0;
-      Ai[p][k] = okx ? a.y : 0.0;
-      Br[p][k] = oky ? ey.x : 0.0;
-      Bi[p][k] = oky ? -ey.y : 0.0;                        // conj(ey)
-    }
-    __syncthreads();
+      __syncthreads();
+      if (na <= 0 || nb <= 0) continue;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      int p = kk * 4 + (lane >> 4);
-      double ar[2], ai[2], br[2], bi[2];
-      for (int a = 0; a < 2; ++a) {
-        ar[a] = Ar[p][wm + a * 16 + (lane & 15)];
-        ai[a] = Ai[p][wm + a * 16 + (lane & 15)];
-        br[a] = Br[p][wn + a * 16 + (lane & 15)];
-        bi[a] = Bi[p][wn + a * 16 + (lane & 15)];
-      }
-      for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b) {
-          acc1[a][b] = mfma16(ar[a], br[b], acc1[a][b]);
-          acc2[a][b] = mfma16(ai[a], bi[b], acc2[a][b]);
-          acc3[a][b] = mfma16(ar[a] + ai[a], br[b] + bi[b], acc3[a][b]);
+      for (int kk = 0; kk < 4; ++kk) {
+        int p = kk * 4 + (lane >> 4);
+        double ar[2], ai[2], br[2], bi[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          ar[a] = Ar[p][wm + a * 16 + (lane & 15)];
+          ai[a] = Ai[p][wm + a * 16 + (lane & 15)];
+          br[a] = Br[p][wn + a * 16 + (lane & 15)];
+          bi[a] = Bi[p][wn + a * 16 + (lane & 15)];
         }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            if (a >= na || b >= nb) continue;
+            acc1[a][b] = mfma16(ar[a], br[b], acc1[a][b]);
+            acc2[a][b] = mfma16(ai[a], bi[b], acc2[a][b]);
+            acc3[a][b] = mfma16(ar[a] + ai[a], br[b] + bi[b], acc3[a][b]);
+          }
+      }
     }
   }
   for (int a = 0; a < 2; ++a)

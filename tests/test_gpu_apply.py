@@ -59,6 +59,24 @@ def test_apply_and_adjoint_parity(nx, ny, mx, my, delta, seed):
     plan.close()
 
 
+@pytest.mark.parametrize("nx,ny,M", [
+    (2, 2, 4), (16, 18, 289), (34, 16, 577),     # blocks of 16 at and past their ends, one tile
+    (64, 66, 4225), (98, 130, 12800),            # tiles of 64 with one and with most blocks empty
+])
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_adjoint_tile_edges(nx, ny, M, nrhs):
+    # row counts around the fills of 32 points and the chunks of 256 rows
+    rng = np.random.default_rng(nx + ny + nrhs)
+    for m in (M, M + 15, M + 16, M + 17, M + 32):
+        pts = rng.random((m, 2))
+        g = complex_normal(rng, (nrhs, m))
+        plan = nd.Plan(pts, nx, ny)
+        ref = onu.apply_adj(pts, g, nx, ny)
+        got = plan.apply_adj(torch.from_numpy(g).to(dev())).cpu().numpy()
+        assert np.max(np.abs(got - ref)) < 1e-13 * np.max(np.abs(ref)), m
+        plan.close()
+
+
 def test_apply_full_size_sampled():
     # n = 512, M = 1024^2: compare 2000 sampled rows of A c and 64 sampled
     # coefficients of A^* f with the oracle evaluated one by one.
