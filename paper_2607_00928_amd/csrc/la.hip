@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_c16_kernel(DS descs, int spli
   }
 }
 
-// Products with 3 or 5 to 16 columns, B not transposed (sweeps with several
+// Products with 2 or 5 to 16 columns, B not transposed (sweeps with several
 // right-hand sides): bound by latency, then by the read of A.  A workgroup
 // takes 16 RT rows of C; its four waves take every fourth chunk of 16 k, each
 // with up to four chunks (8 to 16 KB of A) in flight, straight from memory in
@@ -2774,12 +2774,14 @@ void gemm_batched(DescPool& pool, const std::vector<GemmDesc<T>>& d, Op opA, Op 
       continue;
     }
     // Columns from which gemm_n16_kernel beats the one-column-at-a-time kernels
-    // below (us: op N 9001 x 3 x 256 11 / 21, FP64 17 / 24, but 512 x 240^2 x 3 184
-    // / 146 in FP64; op C 16 x 564^2 FP32 with 4 columns 20 / 18, 5 19 / 26)
-    // and the sizes: op N over many row tiles needs a k that keeps the four waves
-    // busy (1408 products 167 x 8 x 95: 137 / 74 us, 64 of 281 x 8 x 238: 22 / 73)
-    const int n16 = sizeof(T) == 4 && opA == OpN ? 3 : 5;
-    const bool k16 = opA == OpC || maxk >= 192 || (int64_t)ceil_div(maxm, 16) * (int64_t)n <= 512;
+    // below (us, new / old: op N 4 products 3000 x 2 x 256 11 / 15, but 256 of 900 x
+    // 2 x 256 125 / 103 and FP64 512 of 240 x 3 x 240 184 / 146; op C FP32 16 of
+    // 564^2 with 4 columns 20 / 18, with 5 19 / 26) and the sizes: op N over many
+    // row tiles needs a k that keeps the four waves busy (1408 of 167 x 8 x 95: 137
+    // / 74, 64 of 281 x 8 x 238: 22 / 73)
+    const int64_t tiles = (int64_t)ceil_div(maxm, 16) * (int64_t)n;
+    const int n16 = sizeof(T) == 4 && opA == OpN && tiles < 8192 ? 2 : 5;
+    const bool k16 = opA == OpC || maxk >= 192 || tiles <= 512;
     if (splits_force == 0 && maxn >= n16 && maxn <= 16 && opB == OpN && k16 && !lower_any &&
         n16_batched<T>(pool, sub, opA, maxm, maxn, maxk))
       continue;
