@@ -350,7 +350,6 @@ struct QrhLds {
     double2 Q[QR_NB][QR_NB + 1];
     struct {                      // while the columns are factored
       double2 row[2][4][QR_NB];   // pivot row of the Gram, of A1, pivot column of A1, of X
-      double2 rr[4][QR_NB];       // row of R, one copy a wave
     };
   };
   float2 V[QR_NB][QR_NB + 1];     // V1, explicit unit lower
@@ -702,7 +701,10 @@ __global__ __launch_bounds__(256, 2) void qr_half_factor_kernel(
     put((Blk)S.G, t);
     __syncthreads();
   };
-  const bool alone = js < jb;   // workgroup 0 finishes the panel and its updates alone
+  // a panel that split: workgroup 0 finishes it and its updates alone (the tails
+  // are transformed in place)
+  const bool alone = js < jb;
+  if (alone && !first) return;
   while (js < jb) {
     put((Blk)S.X, x);
     __syncthreads();
