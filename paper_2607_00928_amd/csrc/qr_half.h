@@ -355,7 +355,6 @@ struct QrhLds {
   float2 V[QR_NB][QR_NB + 1];     // V1, explicit unit lower
   double2 tau[QR_NB], scal[QR_NB];
   double norm[QR_NB], beta[QR_NB];
-  double wx[2][2];                // sum_i |x_i| ||a_i|| of the pivot column, two halves
 };
 
 // 1 / sqrt(v) and 1 / v of positive normal v: the hardware's estimates and two
@@ -375,96 +374,130 @@ __device__ __forceinline__ double rcp64(double v) {
 
 // t -= p q^T (conj(p) with CJ): one 4-step product for the real and one for the
 // imaginary part; p's rows and q's columns come one a lane (lane % 16), the
-// lanes of k = 0 hold the first term of each product, those of k = 1 the second
+// lanes of k = 0 hold the first term of each product, those of k = 1 the second;
+// q is zero in the lanes of k = 2, 3
 template <bool CJ>
 __device__ __forceinline__ void rank1_sub(Tile& t, double2 p, double2 q) {
-  const int k = (threadIdx.x & 63) >> 4;
-  const double py = CJ ? -p.y : p.y;
-  const double ar = k == 0 ? -p.x : k == 1 ? py : 0.0;
-  const double ai = k == 0 ? -p.x : k == 1 ? -py : 0.0;
-  t.re = mfma16(ar, k == 0 ? q.x : q.y, t.re);
-  t.im = mfma16(ai, k == 0 ? q.y : q.x, t.im);
+  const bool odd = (threadIdx.x & 16) != 0;
+  const double px = -p.x, py = CJ ? -p.y : p.y;
+  const double qa = odd ? q.y : q.x, qb = odd ? q.x : q.y;
+  t.re = mfma16(odd ? py : px, qa, t.re);
+  t.im = mfma16(odd ? -py : px, qb, t.im);
 }
 
 // Panel columns js .. of the blocks: g the Gram over the rows from the pivot
 // on, a the top block (A1 / R / V1), x the tails' transform.  The pivot
 // column's reflector is kept unscaled, (alpha - beta, x): its multiples f are
 // all the other columns need, so a step is three rank-one updates on the
-// matrix cores (0.4 us a step; with one thread per column and four rows, the
-// updates' LDS reads and FP64 instructions took 1.4 us).  Every lane derives
-// the step's scalars and the multiples of one column of its tile.  On return
+// matrix cores; tiles that no later step reads are left as they are.  A step is
+// a chain: of its some 2500 clk the reads of LDS take 300, the split test 270, the
+// scalars 260, the multiples and updates 780, publishing the next pivot 530 and
+// the barrier 350.  So everything uniform is scalar, and a lane derives the
+// multiples of one column of its tile (the wave of the off-diagonal tile of g
+// two): 2800 clk a step before, 8 panels of 600 x 128 66 -> 62 us, 1000 of 300 x 64
+// 345 -> 310.  With the updates one step late, beside the next step's scalars,
+// the corrections of what that step reads cost more than the updates' latency.
+// On return
 // the columns js .. j - 1 of a (rows below the diagonal) and of x are scaled
 // to v_0 = 1 and a's diagonal holds R.  Returns the first column whose Gram has
 // lost too much (QRH_LOSS; jb when none has; column js itself is always taken).
 __device__ inline int qrh_factor(QrhLds& S, Tile& g, Tile& a, Tile& x, int js, int jb) {
-  const int tid = threadIdx.x, lo = tid & 15, ti = tid >> 7;
-  const int c1 = tile_col(), c2 = 16 * ti + lo;
-  double nrow[4];   // the columns' norms at js, for the rows of x
+  const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, hi = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), ti = wave >> 1, tj = wave & 1;
+  const int c1 = 16 * tj + lo, c2 = 16 * ti + lo;
+  const double2 z = make_double2(0.0, 0.0);
+  js = __builtin_amdgcn_readfirstlane(js);
+  jb = __builtin_amdgcn_readfirstlane(jb);
+  // row j of the Gram and of A1, column j of A1 and of X, as the tiles hold them
   auto publish = [&](int j) {
     double2(*p)[QR_NB] = S.row[j & 1];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = tile_row(v);
-      if (i == j) {
-        p[0][c1] = make_double2(g.re[v], g.im[v]);
-        p[1][c1] = make_double2(a.re[v], a.im[v]);
+    if (j >> 4 == ti) {
+      const int w = (j >> 2) & 3;
+      const double2 gv = w == 0   ? make_double2(g.re[0], g.im[0])
+                         : w == 1 ? make_double2(g.re[1], g.im[1])
+                         : w == 2 ? make_double2(g.re[2], g.im[2])
+                                  : make_double2(g.re[3], g.im[3]);
+      const double2 av = w == 0   ? make_double2(a.re[0], a.im[0])
+                         : w == 1 ? make_double2(a.re[1], a.im[1])
+                         : w == 2 ? make_double2(a.re[2], a.im[2])
+                                  : make_double2(a.re[3], a.im[3]);
+      if (hi == (j & 3)) {
+        p[0][c1] = gv;
+        p[1][c1] = av;
       }
-      if (c1 == j) {
-        p[2][i] = i > j ? make_double2(a.re[v], a.im[v]) : make_double2(0.0, 0.0);
+    }
+    if (j >> 4 == tj && lo == (j & 15)) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = 16 * ti + hi + 4 * v;
+        p[2][i] = make_double2(a.re[v], a.im[v]);
         p[3][i] = make_double2(x.re[v], x.im[v]);
       }
     }
-    double w = 0.0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) w = fma(fabs(x.re[v]) + fabs(x.im[v]), nrow[v], w);
-    w += __shfl_xor(w, 16, 64);
-    w += __shfl_xor(w, 32, 64);
-    if (c1 == j && (tid & 63) < 16) S.wx[j & 1][ti] = w;
   };
 #pragma unroll
   for (int v = 0; v < 4; ++v)
     if (tile_row(v) == c1) S.norm[c1] = sqrt(fmax(g.re[v], 0.0));
-  __syncthreads();
-#pragma unroll
-  for (int v = 0; v < 4; ++v) nrow[v] = S.norm[tile_row(v)];
   publish(js);
   __syncthreads();
+  const double n0 = S.norm[lo], n1 = S.norm[16 + lo];   // the columns' norms at js
   int j = js;
   for (; j < jb; ++j) {
     double2(*p)[QR_NB] = S.row[j & 1];
     const double gjj = p[0][j].x;
     const double2 al = p[1][j];
-    const double2 rg1 = p[0][c1], ra1 = p[1][c1], rg2 = p[0][c2], ra2 = p[1][c2];
+    const double2 rg1 = p[0][c1], ra1 = p[1][c1];
     double2 ca = p[2][c2];
-    const double2 cx = p[3][c2];
-    const double wx = S.wx[j & 1][0] + S.wx[j & 1][1];
-    if (j > js && !(gjj >= QRH_LOSS * wx * wx)) break;   // the same values in every thread
+    const double2 x0 = p[3][lo], x1 = p[3][16 + lo], cx = ti ? x1 : x0;
+    // sum_i |x_i| ||a_i|| over the pivot column of X: lane 0's order of the sum, the
+    // same in every wave (all take the same turn below)
+    double wx = fma(fabs(x0.x) + fabs(x0.y), n0, (fabs(x1.x) + fabs(x1.y)) * n1);
+    wx += dpp_get<0x121, 0xF>(wx);
+    wx += dpp_get<0x122, 0xF>(wx);
+    wx += dpp_get<0x124, 0xF>(wx);
+    wx += dpp_get<0x128, 0xF>(wx);
+    if (j > js && __builtin_amdgcn_readfirstlane((int)!(gjj >= QRH_LOSS * wx * wx))) break;
     // squared norm from the pivot on: gjj, and no less than |alpha|^2; beta =
     // -sign(Re alpha) nrm, tau = 1 - conj(alpha) / beta, scal = 1 / (alpha - beta)
-    const double a2 = fma(al.x, al.x, al.y * al.y), n2 = fmax(gjj, a2);
-    const double rn = rsqrt64(n2), nrm = n2 * rn, ax = fabs(al.x);
-    const double id = rcp64(fma(2.0 * nrm, ax, n2 + a2));   // 1 / |alpha - beta|^2
+    const double a2 = fma(al.x, al.x, al.y * al.y), nn = fmax(gjj, a2);
+    const double rn = rsqrt64(nn), nrm = nn * rn, ax = fabs(al.x);
+    const double id = rcp64(fma(2.0 * nrm, ax, nn + a2));   // 1 / |alpha - beta|^2
     const bool none = !(gjj > a2) && al.y == 0.0;           // nothing below the pivot: H = I
     const double beta = none ? al.x : al.x >= 0.0 ? -nrm : nrm;
     const double dx = al.x - beta;
     double2 tau = make_double2(fma(ax, rn, 1.0), al.x >= 0.0 ? al.y * rn : -al.y * rn);
     double2 scal = make_double2(dx * id, -al.y * id);
-    if (none) tau = scal = make_double2(0.0, 0.0);
+    if (__builtin_amdgcn_readfirstlane((int)none)) tau = scal = z;
+    if (tid == 0) {
+      S.tau[j] = tau;
+      S.scal[j] = scal;
+      S.beta[j] = beta;
+    }
     // column c: u = v^H a_c over the reflector's rows, tu = conj(tau) u, its
     // row of R and its multiple f of the unscaled reflector
     auto tu_of = [&](double2 rg, double2 ra) {
       return cmulc(tau, cadd(ra, cmulc(scal, csub(rg, cmulc(al, ra)))));
     };
-    const double2 tu1 = tu_of(rg1, ra1), tu2 = tu_of(rg2, ra2), z = make_double2(0.0, 0.0);
-    const double2 f = c1 > j ? cmul(scal, tu1) : z;
-    if (c2 == j) ca = make_double2(dx, al.y);
-    rank1_sub<false>(a, ca, f);
-    rank1_sub<false>(x, cx, f);
-    rank1_sub<true>(g, c2 > j ? csub(ra2, tu2) : z, c1 > j ? csub(ra1, tu1) : z);
-    if (tid == 0) {
-      S.tau[j] = tau;
-      S.scal[j] = scal;
-      S.beta[j] = beta;
+    if (j < 16 * tj + 15) {   // this wave's columns reach past the pivot
+      const double2 tu1 = tu_of(rg1, ra1);
+      // lanes 32 .. 63 hold k = 2, 3 of the updates: zero
+      const bool on = c1 > j && lane < 32;
+      const double2 f = on ? cmul(scal, tu1) : z;
+      const double2 r1 = on ? csub(ra1, tu1) : z;
+      rank1_sub<false>(x, cx, f);
+      if (j < 16 * ti + 16) {
+        ca = c2 > j ? ca : c2 == j ? make_double2(dx, al.y) : z;
+        rank1_sub<false>(a, ca, f);
+        if (ti <= tj) {
+          double2 r2 = r1;
+          if (ti < tj) {
+            const double2 rg2 = p[0][c2], ra2 = p[1][c2];
+            r2 = csub(ra2, tu_of(rg2, ra2));
+          }
+          if (!(c2 > j)) r2 = z;
+          rank1_sub<true>(g, r2, r1);
+        }
+      }
     }
     if (j + 1 < jb) publish(j + 1);
     __syncthreads();
@@ -492,6 +525,31 @@ __device__ inline int qrh_factor(QrhLds& S, Tile& g, Tile& a, Tile& x, int js, i
   return j;
 }
 
+// The s x s blocks right of each even inverted s x s diagonal block of the unit
+// upper triangle S.G: B <- -M1 (B M2); 16 s entries, one a thread.  The sums run
+// over whole blocks (the triangles' zeros are stored), so that their reads of
+// LDS go out together.
+template <int s>
+__device__ inline void qrh_inv_level(QrhLds& S) {
+  const int tid = threadIdx.x, blk = tid / (s * s), e = tid % (s * s);
+  const int i = e % s, c = e / s, r0 = 2 * s * blk, c0 = r0 + s;
+  const bool on = tid < 16 * s;
+  __syncthreads();
+  if (on) {
+    double2 t = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int k = 0; k < s; ++k) t = cadd(t, cmul(S.G[r0 + i][c0 + k], S.G[c0 + k][c0 + c]));
+    S.Q[r0 + i][c0 + c] = t;
+  }
+  __syncthreads();
+  if (on) {
+    double2 t = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int k = 0; k < s; ++k) t = cadd(t, cmul(S.G[r0 + i][r0 + k], S.Q[r0 + k][c0 + c]));
+    S.G[r0 + i][c0 + c] = make_double2(-t.x, -t.y);
+  }
+}
+
 // S.G holds V^H V (32 x 32): replaced by T = (I + D striu(V^H V))^{-1} D, D =
 // diag(tau), the unit upper triangle inverted by doubling its inverted blocks
 __device__ inline void qrh_t_factor(QrhLds& S) {
@@ -501,25 +559,11 @@ __device__ inline void qrh_t_factor(QrhLds& S) {
     const double2 z = make_double2(0.0, 0.0);
     S.G[i][c] = i < c ? cmul(S.tau[i], S.G[i][c]) : i == c ? make_double2(1.0, 0.0) : z;
   }
-  for (int s = 1; s < QR_NB; s *= 2) {
-    // the s x s blocks right of each even inverted block: B <- -M1 (B M2);
-    // 16 s entries, one a thread
-    const int nb = s * s, blk = tid / nb, e = tid % nb;
-    const int i = e % s, c = e / s, r0 = 2 * s * blk, c0 = r0 + s;
-    const bool on = tid < 16 * s;
-    __syncthreads();
-    if (on) {
-      double2 t = make_double2(0.0, 0.0);
-      for (int k = 0; k <= c; ++k) t = cadd(t, cmul(S.G[r0 + i][c0 + k], S.G[c0 + k][c0 + c]));
-      S.Q[r0 + i][c0 + c] = t;
-    }
-    __syncthreads();
-    if (on) {
-      double2 t = make_double2(0.0, 0.0);
-      for (int k = i; k < s; ++k) t = cadd(t, cmul(S.G[r0 + i][r0 + k], S.Q[r0 + k][c0 + c]));
-      S.G[r0 + i][c0 + c] = make_double2(-t.x, -t.y);
-    }
-  }
+  qrh_inv_level<1>(S);
+  qrh_inv_level<2>(S);
+  qrh_inv_level<4>(S);
+  qrh_inv_level<8>(S);
+  qrh_inv_level<16>(S);
   __syncthreads();
   for (int e = tid; e < QR_NB * QR_NB; e += 256) {
     const int i = e & 31, c = e >> 5;
