@@ -171,7 +171,7 @@ static void test_geqrf(int nb, const int32_t* mn, const int32_t* ld, const int64
     d[i] = QRDesc<T>{mn[2 * i], mn[2 * i + 1], ld[2 * i], ld[2 * i + 1], (cplx<T>*)ptrs[3 * i],
                      (cplx<T>*)ptrs[3 * i + 1], (cplx<T>*)ptrs[3 * i + 2]};
   DescPool pool;
-  pool.init(16 << 20, nullptr);
+  pool.init(4096, nullptr, 16 << 20);   // grows with the lists
   void* ws;
   ND_HIP(hipMalloc(&ws, qr_workspace<T>(d)));
   geqrf_batched<T>(pool, d, ws, graded);
@@ -188,7 +188,7 @@ static void test_ormqr(int trans, int nb, const int32_t* dims, const int32_t* ld
                       (const cplx<T>*)ptrs[3 * i], (const cplx<T>*)ptrs[3 * i + 1],
                       (cplx<T>*)ptrs[3 * i + 2]};
   DescPool pool;
-  pool.init(16 << 20, nullptr);
+  pool.init(4096, nullptr, 16 << 20);
   void* ws;
   ND_HIP(hipMalloc(&ws, orm_workspace<T>(d)));
   ormqr_batched<T>(pool, d, trans == 1, ws, trans == 2);

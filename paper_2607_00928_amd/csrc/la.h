@@ -25,7 +25,11 @@ struct DescPool {
   // so a stream capture records no copies and no waits; flush() then uploads
   // everything staged (the descriptors stay valid for the graph's lifetime)
   bool deferred = false;
-  void init(size_t bytes, hipStream_t s);
+  // Starts with `bytes` and grows to at most `limit` (0: `bytes`): a list that
+  // does not fit opens a larger segment, and the full one stays until the next
+  // sync_reset(), since launches in flight read it.  Pinning 256 MiB at once took
+  // 1.5 ms of every factorization; most use a few MiB.
+  void init(size_t bytes, hipStream_t s, size_t limit = 0);
   void destroy();
   void check_flag();   // synchronises; E_INTERNAL if the flag is set
   // copies n bytes to the device, returns the device address
@@ -48,10 +52,17 @@ struct DescPool {
   void* stream_scratch(size_t n);
   char* sscr = nullptr;
   size_t sscr_cap = 0;
+  struct Segment {
+    char *host, *dev;
+  };
+  std::vector<Segment> full;   // segments outgrown since the last sync_reset()
+  size_t spent = 0, most = 0;  // bytes used in them; limit of the bytes in use
   size_t valid = 0;        // slots [0, valid) mirror the host staging on the device
   bool tainted = false;    // a plain push happened: no reuse
   void flush();
   void sync_reset();
+  // room for n bytes (rounded up to a slot) in the current segment
+  void make_room(size_t n);
   // take over o's buffers and state (o is left empty); the current ones are
   // released first
   void adopt(DescPool& o);

@@ -23,9 +23,10 @@ namespace nd {
 thread_local bool g_fp32_split = true;
 
 // ------------------------------------------------------------ descriptor pool
-void DescPool::init(size_t bytes, hipStream_t s) {
+void DescPool::init(size_t bytes, hipStream_t s, size_t limit) {
   destroy();
   cap = bytes;
+  most = std::max(bytes, limit);
   stream = s;
   valid = 0;
   tainted = false;
@@ -34,6 +35,28 @@ void DescPool::init(size_t bytes, hipStream_t s) {
   flag = (int*)(dev + cap);
   ND_HIP(hipMemsetAsync(flag, 0, sizeof(int), stream));
   used = 0;
+}
+
+void DescPool::make_room(size_t n) {
+  if (used + n <= cap) return;
+  ND_CHECK(!deferred && spent + used + n <= most, NUDFT2_E_INTERNAL,
+           "descriptor pool exhausted");
+  const size_t c = std::max(std::min(4 * cap, most - spent - used), n);
+  Segment s{nullptr, nullptr};
+  ND_HIP(hipHostMalloc((void**)&s.host, c, hipHostMallocDefault));
+  const hipError_t e = hipMalloc((void**)&s.dev, c + 256);
+  if (e != hipSuccess) (void)hipHostFree(s.host);
+  ND_HIP(e);
+  full.push_back({host, dev});
+  host = s.host;
+  dev = s.dev;
+  spent += used;
+  cap = c;
+  used = valid = 0;
+  // the error flag moves along, behind the launches that may set the old one
+  int* f = (int*)(dev + cap);
+  ND_HIP(hipMemcpyAsync(f, flag, sizeof(int), hipMemcpyDeviceToDevice, stream));
+  flag = f;
 }
 
 void DescPool::check_flag() {
@@ -47,10 +70,15 @@ void DescPool::destroy() {
   if (host) (void)hipHostFree(host);
   if (dev) (void)hipFree(dev);
   if (sscr) (void)hipFree(sscr);
+  for (Segment& q : full) {
+    (void)hipHostFree(q.host);
+    (void)hipFree(q.dev);
+  }
+  full.clear();
   host = dev = sscr = nullptr;
   sscr_cap = 0;
   flag = nullptr;
-  cap = used = 0;
+  cap = used = spent = most = 0;
 }
 
 void DescPool::adopt(DescPool& o) {
@@ -65,17 +93,26 @@ void DescPool::adopt(DescPool& o) {
   deferred = o.deferred;
   sscr = o.sscr;
   sscr_cap = o.sscr_cap;
+  full.swap(o.full);
+  spent = o.spent;
+  most = o.most;
   valid = o.valid;
   tainted = o.tainted;
   o.host = o.dev = o.sscr = nullptr;
   o.flag = nullptr;
-  o.cap = o.used = o.sscr_cap = o.valid = 0;
+  o.cap = o.used = o.sscr_cap = o.spent = o.most = o.valid = 0;
   o.tainted = false;
 }
 
 void DescPool::sync_reset() {
   if (deferred) return;
   ND_HIP(hipStreamSynchronize(stream));
+  for (Segment& q : full) {
+    (void)hipHostFree(q.host);
+    (void)hipFree(q.dev);
+  }
+  full.clear();
+  spent = 0;
   // after a plain push the device copy may differ from the staging (kernel
   // scratch): nothing is reusable until the next cycle has uploaded again
   if (!tainted) valid = std::max(valid, used);
@@ -99,7 +136,7 @@ void* DescPool::push_ro(const void* src, size_t n) {
 void* DescPool::push(const void* src, size_t n) {
   tainted = true;
   size_t need = (n + 255) & ~size_t(255);
-  ND_CHECK(used + need <= cap, NUDFT2_E_INTERNAL, "descriptor pool exhausted");
+  make_room(need);
   std::memcpy(host + used, src, n);
   if (!deferred) ND_HIP(hipMemcpyAsync(dev + used, host + used, n, hipMemcpyHostToDevice, stream));
   void* d = dev + used;
@@ -110,7 +147,7 @@ void* DescPool::push(const void* src, size_t n) {
 void* DescPool::reserve(size_t n) {
   tainted = true;
   size_t need = (n + 255) & ~size_t(255);
-  ND_CHECK(used + need <= cap, NUDFT2_E_INTERNAL, "descriptor pool exhausted");
+  make_room(need);
   void* d = dev + used;
   used += need;
   return d;
@@ -2973,8 +3010,8 @@ void qr_panel_launch(DescPool& pool, const QRDesc<T>* dd, const std::vector<int>
   unsigned* bar = (unsigned*)(z + scr_bytes);
   hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)std::min<size_t>((words + 255) / 256, 1024)),
                      dim3(256), 0, pool.stream, (unsigned*)z, (int64_t)words);
-  int* err = pool.flag;
   with_descs(pool, act.data(), act.size(), [&](auto as) {
+    int* err = pool.flag;   // after the list's upload, which may move the pool
     const void* k = tall ? (const void*)qr_panel_kernel<T, decltype(as), 2>
                          : (const void*)qr_panel_kernel<T, decltype(as), 1>;
     void* args[] = {(void*)&dd, (void*)&as, (void*)&nact, (void*)&j0, (void*)&gsize,

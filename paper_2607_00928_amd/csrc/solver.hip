@@ -360,7 +360,7 @@ void factor_t(Plan* P) {
   Ctx cx;
   cx.P = P;
   cx.s = P->stream;
-  cx.pool.init(256 << 20, cx.s);
+  cx.pool.init(8 << 20, cx.s, 256 << 20);
   std::unique_ptr<HSS2<T>> H(new HSS2<T>());
   H->precision = std::is_same<T, float>::value ? 1 : 0;
   ND_HIP(hipStreamSynchronize(cx.s));
@@ -533,7 +533,7 @@ struct SolveCtx {
   SolveCtx(Plan* p, int nr) : P(p), H(*static_cast<HSS2<T>*>(p->hss.get())), nrhs(nr) {
     cx.P = P;
     cx.s = P->stream;
-    if (!P->spool.host) P->spool.init(64 << 20, cx.s);
+    if (!P->spool.host) P->spool.init(4 << 20, cx.s, 64 << 20);
     cx.pool.adopt(P->spool);
     cx.pool.sync_reset();
     w.fw = (cplx<T>*)cx.tmp_alloc(sizeof(cplx<T>) * P->Mtot * nrhs);

@@ -429,6 +429,34 @@ def test_pchol_greedy(sizes):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("nb", [1, 43, 400])
+def test_qr_descriptor_lists_outgrow_the_pool(prec, nb):
+    """The hooks' descriptor pool starts at 4 KiB: lists too long for kernel
+    arguments move it to larger segments again and again during one batch (and
+    FP64's error flag with it), behind launches that read the old ones."""
+    rng = np.random.default_rng(31 + nb)
+    m, n = 150, 136
+    A = crandn(rng, nb, m, n)
+    tA = torch.from_numpy(np.ascontiguousarray(A.transpose(0, 2, 1)).astype(CT[prec][0])).to(DEV)
+    A = tA.cpu().numpy().transpose(0, 2, 1).astype(np.complex128)
+    tR = torch.zeros((nb, n, n), dtype=CT[prec][1], device=DEV)
+    tT = torch.zeros((nb, n * n), dtype=CT[prec][1], device=DEV)
+    tQ = torch.eye(m, dtype=CT[prec][1], device=DEV).repeat(nb, 1, 1)
+    a1, p1 = i32([m, n] * nb)
+    a2, p2 = i32([m, n] * nb)
+    a3, p3 = i64(sum([[t[b].data_ptr() for t in (tA, tR, tT)] for b in range(nb)], []))
+    assert lib.nudft2_test_geqrf(prec, nb, p1, p2, p3) == 0, lib.nudft2_last_error()
+    b1, q1 = i32([m, n, m] * nb)
+    b2, q2 = i32([m, m] * nb)
+    b3, q3 = i64(sum([[t[b].data_ptr() for t in (tA, tT, tQ)] for b in range(nb)], []))
+    assert lib.nudft2_test_ormqr(prec, 0, nb, q1, q2, q3) == 0, lib.nudft2_last_error()
+    Q = tQ.cpu().numpy().transpose(0, 2, 1).astype(np.complex128)
+    R = tR.cpu().numpy().transpose(0, 2, 1).astype(np.complex128)
+    err = np.abs(Q[:, :, :n] @ R - A).max(axis=(1, 2)) / np.abs(A).max(axis=(1, 2))
+    assert err.max() < 50 * TOL[prec] * np.sqrt(m)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("ct", [0, 1])
 def test_trsv(prec, ct):
     rng = np.random.default_rng(11 + ct)
