@@ -109,42 +109,50 @@ __device__ __forceinline__ int tile_col() {
 }
 // One step's rows of the Gram of the first QR_NB columns of An (their rows from
 // jb on, counted from the panel's first) against all 16 ctile: wave w takes the
-// column tiles w, w + 4.
+// rows' half w % 2 against column tiles w / 2, w / 2 + 2, ..., so that all four
+// have work from two tiles on (with a wave per column tile two had none at the
+// end of a half: 1000 of 300 x 64 with the columns' update 299 -> 267 us).
 __device__ __forceinline__ void qrh_gram_step(const float2 (&An)[QR_HB][QRH_LD], int ctile, int r0,
-                                              int jb, dbl4 (&gr)[2][2], dbl4 (&gi)[2][2]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lo = lane & 15, hi = lane >> 4;
+                                              int jb, dbl4 (&gr)[4], dbl4 (&gi)[4]) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lo = lane & 15, hi = lane >> 4, a = wave & 1;
+  if (a >= ctile) return;
+  auto rows = [&](int s) {
+    const int r = 4 * s + hi;
+    double2 v = make_double2(0.0, 0.0);
+    if (r0 + r >= jb) v = widen(An[16 * a + lo][r]);
+    v.y = -v.y;
+    return v;
+  };
+  // two tiles at a time (four chains of matrix instructions), then one
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int tile = wave + 4 * t;
-    if (tile >= ctile) continue;
+  for (int t = 0; t < 4; t += 2) {
+    const int tile = (wave >> 1) + 2 * t;
+    if (tile + 2 < ctile) {
 #pragma unroll 4
-    for (int s = 0; s < QRH_ROWS / 4; ++s) {
-      const int r = 4 * s + hi;
-      const double2 b = widen(An[16 * tile + lo][r]);
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        double2 v = make_double2(0.0, 0.0);
-        if (r0 + r >= jb && a < ctile) v = widen(An[16 * a + lo][r]);
-        v.y = -v.y;
-        mfma_c(v, b, gr[t][a], gi[t][a]);
+      for (int s = 0; s < QRH_ROWS / 4; ++s) {
+        const double2 v = rows(s);
+        mfma_c(v, widen(An[16 * tile + lo][4 * s + hi]), gr[t], gi[t]);
+        mfma_c(v, widen(An[16 * tile + 32 + lo][4 * s + hi]), gr[t + 1], gi[t + 1]);
       }
+    } else if (tile < ctile) {
+#pragma unroll 4
+      for (int s = 0; s < QRH_ROWS / 4; ++s)
+        mfma_c(rows(s), widen(An[16 * tile + lo][4 * s + hi]), gr[t], gi[t]);
     }
   }
 }
-__device__ __forceinline__ void qrh_gram_store(double2* part, int ctile, const dbl4 (&gr)[2][2],
-                                               const dbl4 (&gi)[2][2]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ void qrh_gram_store(double2* part, int ctile, const dbl4 (&gr)[4],
+                                               const dbl4 (&gi)[4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = wave & 1;
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int tile = wave + 4 * t;
+  for (int t = 0; t < 4; ++t) {
+    const int tile = (wave >> 1) + 2 * t;
     if (tile >= ctile) continue;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        stc(part + 16 * a + (lane >> 4) + 4 * v + (size_t)QR_NB * (16 * tile + (lane & 15)),
-            make_double2(gr[t][a][v], gi[t][a][v]));
+    for (int v = 0; v < 4; ++v)
+      stc(part + 16 * a + (lane >> 4) + 4 * v + (size_t)QR_NB * (16 * tile + (lane & 15)),
+          make_double2(gr[t][v], gi[t][v]));
   }
 }
 
@@ -186,11 +194,9 @@ __global__ __launch_bounds__(256, 2) void qr_half_rows_kernel(
                                                   : make_double2(0.0, 0.0);
       }
   }
-  dbl4 gr[2][2], gi[2][2];
+  dbl4 gr[4], gi[4];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int a = 0; a < 2; ++a) gr[t][a] = gi[t][a] = dbl4{0, 0, 0, 0};
+  for (int t = 0; t < 4; ++t) gr[t] = gi[t] = dbl4{0, 0, 0, 0};
   float2* Ap = d.A + rb + (int64_t)j0 * d.lda;         // the panel's tail
   float2* Ac = d.A + rb + (int64_t)rb * d.lda;         // the remaining columns
   const int r1 = min(rows, ((int)blockIdx.x + 1) * per * QRH_ROWS);
@@ -277,11 +283,9 @@ __global__ __launch_bounds__(256, 2) void qr_half_split_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = lane & 15, hi = lane >> 4;
   float2* Ap = d.A + j0 + (int64_t)j0 * d.lda;
-  dbl4 gr[2][2], gi[2][2];
+  dbl4 gr[4], gi[4];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int a = 0; a < 2; ++a) gr[t][a] = gi[t][a] = dbl4{0, 0, 0, 0};
+  for (int t = 0; t < 4; ++t) gr[t] = gi[t] = dbl4{0, 0, 0, 0};
   const int r1 = min(rows, ((int)blockIdx.x + 1) * per * QRH_ROWS);
   for (int r0 = blockIdx.x * per * QRH_ROWS; r0 < r1; r0 += QRH_ROWS) {
     __syncthreads();
