@@ -2826,6 +2826,30 @@ void gemm_batched(DescPool& pool, const std::vector<GemmDesc<T>>& d, Op opA, Op 
       skinny_batched<T>(pool, sub, opA, maxm, maxn, maxk, force);
       continue;
     }
+    // A^H B with few rows of C (the products V^H C of a panel's update): blocks of
+    // 16 columns on gemm_n16_kernel, which reads A once a block; the 64 x 64 tiles
+    // leave a workgroup or two to walk the whole k (32 x 96 x 512 FP64: 15 / 94 us,
+    // 16 of them 22 / 95, FP32 15 / 34).  With many blocks the tiles fill the device
+    // themselves and win for short k (128 products 32 x 96 x 128: 45 / 38, FP32 33 /
+    // 20), in FP32 for any (k = 1500: 102 / 93; FP64 178 / 237).
+    const int cb = ceil_div(maxn, 16);
+    const int64_t nblk = (int64_t)n * cb;
+    const int cbk = nblk <= (sizeof(T) == 8 ? 128 : 32) ? 16 : nblk <= 128 ? 64 : 256;
+    if (splits_force == 0 && opA == OpC && opB == OpN && maxm <= 32 && maxn > 16 && maxn <= 128 &&
+        maxk >= cbk && nblk <= (sizeof(T) == 8 ? 65535 : 512) && !lower_any) {
+      std::vector<GemmDesc<T>> blk;
+      blk.reserve(nblk);
+      for (const auto& g : sub)
+        for (int j = 0; j < g.n; j += 16) {
+          GemmDesc<T> q = g;
+          q.n = std::min(16, g.n - j);
+          q.B = g.B + (int64_t)j * g.ldb;
+          q.C = g.C + (int64_t)j * g.ldc;
+          q.trib = 0;
+          blk.push_back(q);
+        }
+      if (n16_batched<T>(pool, blk, opA, maxm, 16, maxk)) continue;
+    }
     // Splitting the k loop.  The device holds `slots` tile workgroups at once.
     // Long k (>= 4096) with at least 16 output tiles a product: about seven
     // rounds of workgroups, each split at least 2048 long; where that still

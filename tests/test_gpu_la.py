@@ -162,6 +162,9 @@ def test_gemm_skinny(prec, opa, beta):
     [(256, 16, 9001), (31, 10, 1024), (16, 12, 300)],
     # 32 rows a workgroup
     [(65521, 9, 200)],
+    # op C with few rows: blocks of 16 columns, also with k ranges
+    [(32, 96, 700), (7, 17, 33), (1, 128, 300), (20, 33, 2), (16, 40, 0), (31, 5, 90)],
+    [(32, 65, 2500), (9, 128, 1100)],
 ])
 def test_gemm_up_to_16_columns(prec, opa, shapes):
     """Entrywise against the FP64 product (FP64: of the oracle's rounding),
