@@ -303,7 +303,8 @@ constexpr int64_t ADJ_WG_TARGET = 1024;  // workgroups per problem launch wanted
 // partial buffer of cap bytes holds; 0 when not even one chunk fits.  A chunk
 // costs a pass over its partial vector, about 40 rows' worth of products, so
 // it has at least 256 rows: 96 x 160, M = 23 040, three right-hand sides takes
-// 283 us in 56 chunks, 389 us in the 12 of at least 2048 rows (216
+// 258 us in 56 chunks; 283 and 389 us, with the phase tables of the time, in 56
+// and in the 12 of at least 2048 rows (216
 // workgroups, one wave per SIMD); n = 512 the same in 16 and 32 chunks.
 int adj_chunks(const Plan* P, int nrhs, size_t cap) {
   int64_t want = 1;

@@ -1234,7 +1234,8 @@ __global__ __launch_bounds__(256) void gemm_n16_kernel(DS descs, int splits, cpl
   const int i = tid & 15, j = tid >> 4;
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    const C2 v = cadd(cadd(red[0][r][j][i], red[1][r][j][i]), cadd(red[2][r][j][i], red[3][r][j][i]));
+    const C2 v = cadd(cadd(red[0][r][j][i], red[1][r][j][i]),
+                      cadd(red[2][r][j][i], red[3][r][j][i]));
     if (part)
       part[(((size_t)blockIdx.y * splits + blockIdx.z) * gridDim.x + blockIdx.x) * (256 * RT) +
            256 * r + tid] = v;
@@ -1462,8 +1463,8 @@ __global__ void gemm_prescale_kernel(DS descs) {
 // compact-WY factor T (Q_panel = I - V T V^H) and the explicit V / R split
 // described in la.h.
 //
-// FP64 panel factorization (FP32 panels: qr_half.h): a group of gsize workgroups factors one problem's
-// panel; workgroup w of the group holds panel rows [w 128 R, (w+1) 128 R)
+// FP64 panel factorization (FP32 panels: qr_half.h): a group of gsize
+// workgroups factors one problem's panel; workgroup w of the group holds panel rows [w 128 R, (w+1) 128 R)
 // in registers.  Wave v of a workgroup owns the column group v / 2 (QP_CG
 // consecutive columns) on the row half v % 2; lane l of it holds rows
 // half * 64 QP_R + l + 64 k (k < QP_R) of those columns, so loads and stores

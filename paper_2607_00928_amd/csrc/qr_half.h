@@ -18,8 +18,8 @@
 // with A2 are FP64, only A, V, R and T are rounded to FP32.  The squared norm
 // left in column j, g = x^H G x with x = X e_j before scaling, carries the
 // rounding of G's entries, about 1e-16 (sum_i |x_i| ||a_i||)^2.  Where that
-// exceeds 3e-8 g (half of FP32's rounding; QRH_LOSS) the panel is split: the reflectors before column j are applied to the
-// tails, and the rest goes on from a new Gram: by the row pass and another
+// exceeds 3e-8 g (half of FP32's rounding; QRH_LOSS) the panel is split: the
+// reflectors before column j are applied to the tails, and the rest goes on from a new Gram: by the row pass and another
 // factorization launch where the caller expects such panels (the face-split
 // generators of the first recompression stage, whose panels lose three to
 // seven digits), else by the factorization's workgroup itself.
@@ -46,7 +46,8 @@ constexpr int QRH_MAXC = 32;             // most row chunks (partial Grams) of a
 
 // A problem's scratch: the block W, W2, S of geqrf's workspace, which only the
 // steps between halves use.  xy: [X | Y] (QR_NB x QRH_W, leading dimension
-// QR_NB); a1: the panel's top rows (QR_NB x QRH_W); part: partial Grams, QR_NB x ncw each.
+// QR_NB); a1: the panel's top rows (QR_NB x QRH_W); part: partial Grams,
+// QR_NB x ncw each.
 // A split panel's state between its passes: the top block, the reflectors' tau
 // and the first column left (jb: the panel is done).
 struct QrhState {
@@ -401,8 +402,7 @@ __device__ __forceinline__ void rank1_sub(Tile& t, double2 p, double2 q) {
 // two): 2800 clk a step before, 8 panels of 600 x 128 66 -> 62 us, 1000 of 300 x 64
 // 345 -> 310.  With the updates one step late, beside the next step's scalars,
 // the corrections of what that step reads cost more than the updates' latency.
-// On return
-// the columns js .. j - 1 of a (rows below the diagonal) and of x are scaled
+// On return the columns js .. j - 1 of a (rows below the diagonal) and of x are scaled
 // to v_0 = 1 and a's diagonal holds R.  Returns the first column whose Gram has
 // lost too much (QRH_LOSS; jb when none has; column js itself is always taken).
 __device__ inline int qrh_factor(QrhLds& S, Tile& g, Tile& a, Tile& x, int js, int jb) {
