@@ -169,14 +169,13 @@ constexpr int AP = 32;     // points per fill of the phase tables
 // with four of them and the others waiting with two: 96 x 160, M = 23 040, three
 // right-hand sides 294 -> 272 us, 512 x 512, M = 393 216 13.9 -> 13.3 ms; three
 // workgroups a CU with smaller tables are slower, 316 us and 15.1 ms).
-// part[(chunk nrhs + rhs) Ntot + c0 + kx ny + ky] =
+// part[(chunk nrhs + rhs) nx ny + kx ny + ky] =
 //     sum_{j in chunk} conj(Ax[j][kx]) f_j conj(Ay[j][ky])
 // for the chunk of rows [blockIdx.y rows, (blockIdx.y + 1) rows); every entry
 // of the problem's partial vector is stored by exactly one workgroup.
 __global__ __launch_bounds__(256, 2) void apply_adj_kernel(
     const double* __restrict__ pts, const double2* __restrict__ f,
-    double2* __restrict__ part, ApplyProb pr, int64_t Mtot, int64_t Ntot, int64_t rows,
-    int nrhs) {
+    double2* __restrict__ part, ApplyProb pr, int64_t Mtot, int64_t rows, int nrhs) {
   __shared__ double Ar[AK][AT + 1], Ai[AK][AT + 1];
   __shared__ double Br[AK][AT + 1], Bi[AK][AT + 1];
   __shared__ double2 tb[AP][40 + 1];   // a point's phases: 16 of x, 16 of y, 4 bases each
@@ -188,7 +187,7 @@ __global__ __launch_bounds__(256, 2) void apply_adj_kernel(
   const int64_t j0 = (int64_t)blockIdx.y * rows;
   const int rhs = blockIdx.z;
   const double2* fp = f + rhs * Mtot + pr.m0;
-  double2* cp = part + ((int64_t)blockIdx.y * nrhs + rhs) * Ntot + pr.c0;
+  double2* cp = part + ((int64_t)blockIdx.y * nrhs + rhs) * pr.nx * pr.ny;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;   // wave's 32x32 sub-tile
   const int nx = pr.nx, ny = pr.ny;
@@ -283,54 +282,76 @@ __global__ void adj_reduce_kernel(const double2* __restrict__ part, double2* __r
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * nrhs;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int r = (int)(e / n);
-    const int64_t i = pr.c0 + e % n;
+    const int64_t i = e % n;
     double sr = 0.0, si = 0.0;
     for (int ch = 0; ch < nch; ++ch) {
-      const double2 v = part[((int64_t)ch * nrhs + r) * Ntot + i];
+      const double2 v = part[((int64_t)ch * nrhs + r) * n + i];
       sr += v.x;
       si += v.y;
     }
-    c[(int64_t)r * Ntot + i] = mk<double>(sr, si);
+    c[(int64_t)r * Ntot + pr.c0 + i] = mk<double>(sr, si);
   }
 }
 
 constexpr int64_t ADJ_MIN_ROWS = 256;    // rows per chunk, at least
 constexpr int64_t ADJ_WG_TARGET = 1024;  // workgroups per problem launch wanted
 
-// Row chunks of the adjoint apply for a plan: as many as fill the device with
-// whole rounds (ADJ_WG_TARGET workgroups per problem over its tiles and
-// right-hand sides: two rounds of two workgroups a CU) but no more than the
-// partial buffer of cap bytes holds; 0 when not even one chunk fits.  A chunk
-// costs a pass over its partial vector, about 40 rows' worth of products, so
-// it has at least 256 rows: 96 x 160, M = 23 040, three right-hand sides takes
-// 258 us in 56 chunks; 283 and 389 us, with the phase tables of the time, in 56
-// and in the 12 of at least 2048 rows (216
-// workgroups, one wave per SIMD); n = 512 the same in 16 and 32 chunks.
-int adj_chunks(const Plan* P, int nrhs, size_t cap) {
-  int64_t want = 1;
-  for (const Problem& q : P->probs) {
-    const int64_t tiles = (int64_t)ceil_div(q.nx, AT) * ceil_div(q.ny, AT);
-    const int64_t by_rows = std::max<int64_t>(1, (q.M + ADJ_MIN_ROWS - 1) / ADJ_MIN_ROWS);
-    want = std::max(want, std::min(by_rows, ADJ_WG_TARGET / (tiles * nrhs)));
-  }
-  const size_t per_chunk = sizeof(double2) * (size_t)P->Ntot * (size_t)nrhs;
-  const int64_t fit = per_chunk ? (int64_t)(cap / per_chunk) : want;
-  return (int)std::min<int64_t>(want, fit);
+int adj_tiles(const Problem& q) { return ceil_div(q.nx, AT) * ceil_div(q.ny, AT); }
+
+// Row chunks that every problem of a plan gets: chunks of 2048 rows or more
+// until the problem with the most of them has 2048 workgroups a right-hand
+// side, and no more vectors of all coefficients than 256 MiB hold.
+constexpr size_t ADJ_PART_CAP = size_t(256) << 20;
+int64_t adj_base_chunks(const Plan* P, int nrhs) {
+  int64_t base = 1;
+  for (const Problem& q : P->probs)
+    base = std::max<int64_t>(base, std::min<int64_t>(ceil_div(q.M, 2048),
+                                                     ceil_div(2048, adj_tiles(q))));
+  const size_t vec = sizeof(double2) * (size_t)P->Ntot * (size_t)nrhs;
+  return std::max<int64_t>(1, std::min<int64_t>(base, (int64_t)(ADJ_PART_CAP / vec)));
 }
 
-// the adjoint apply with its partials in part (nch chunks, see adj_chunks)
-void apply_adj_into(Plan* P, const double2* f, double2* c, int nrhs, double2* part, int nch,
+// Row chunks of one problem: as many as fill the device with whole rounds
+// (ADJ_WG_TARGET workgroups over its tiles and right-hand sides: two rounds of
+// two workgroups a CU), of at least 256 rows, since a chunk costs a pass over
+// its partial vector, about 40 rows' worth of products; no fewer than the
+// plan's base, whose smaller shares even out the end of a long launch; and no
+// more than the partials of one problem leave room for in `budget` bytes.
+// 96 x 160, M = 23 040, three right-hand sides takes 258 us in 56 chunks, 389
+// us (with slower phase tables) in the base's 12.
+int adj_chunks(const Problem& q, int nrhs, int64_t base, size_t budget) {
+  const int64_t fill = std::min<int64_t>(ceil_div(q.M, ADJ_MIN_ROWS),
+                                         ADJ_WG_TARGET / ((int64_t)adj_tiles(q) * nrhs));
+  const size_t one = sizeof(double2) * (size_t)q.N() * (size_t)nrhs;
+  const int64_t fit = one ? (int64_t)(budget / one) : 1;
+  return (int)std::max<int64_t>(1, std::min(std::max(fill, base), fit));
+}
+
+// bytes of the partials: the problems' launches follow each other on the
+// stream and share them, so the largest problem's count
+size_t adj_part_need(const Plan* P, int nrhs, size_t budget) {
+  const int64_t base = adj_base_chunks(P, nrhs);
+  size_t need = 0;
+  for (const Problem& q : P->probs)
+    need = std::max(need, sizeof(double2) * (size_t)q.N() * (size_t)nrhs *
+                              (size_t)adj_chunks(q, nrhs, base, budget));
+  return need;
+}
+
+// the adjoint apply with its partials in the `budget` bytes at part
+void apply_adj_into(Plan* P, const double2* f, double2* c, int nrhs, double2* part, size_t budget,
                     hipStream_t s) {
+  const int64_t base = adj_base_chunks(P, nrhs);
   for (const Problem& q : P->probs) {
     ApplyProb pr{q.m0, q.M, q.c0, q.nx, q.ny};
-    const int tiles = ceil_div(q.nx, AT) * ceil_div(q.ny, AT);
+    const int nch = adj_chunks(q, nrhs, base, budget);
     // rows per chunk: a multiple of the stage height, nch chunks cover M
     int64_t rows = std::max<int64_t>(AK, (q.M + nch - 1) / nch);
     rows = (rows + AK - 1) / AK * AK;
     const int nchp = std::max(1, ceil_div(q.M, rows));
-    dim3 grid(tiles, nchp, nrhs);
+    dim3 grid(adj_tiles(q), nchp, nrhs);
     hipLaunchKernelGGL(apply_adj_kernel, grid, dim3(256), 0, s, P->pts_user, f, part, pr,
-                       P->Mtot, P->Ntot, rows, nrhs);
+                       P->Mtot, rows, nrhs);
     const int64_t n = q.N() * nrhs;
     hipLaunchKernelGGL(adj_reduce_kernel,
                        dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (n + 255) / 256))),
@@ -387,15 +408,15 @@ double2* scratch_addr(int dev) {
 }  // namespace
 
 void apply_adj_noalloc(Plan* P, const double2* f, double2* c, int nrhs) {
-  const int nch = adj_chunks(P, nrhs, NOALLOC_SCRATCH_BYTES);
-  ND_CHECK(nch >= 1, NUDFT2_E_INVAL,
+  ND_CHECK(sizeof(double2) * (size_t)P->Ntot * (size_t)nrhs <= NOALLOC_SCRATCH_BYTES,
+           NUDFT2_E_INVAL,
            "nrhs * N * 16 bytes exceeds the 64 MiB scratch of the no-allocation adjoint");
   int cur = -1;
   ND_HIP(hipGetDevice(&cur));
   const bool switch_dev = cur != P->device;
   if (switch_dev) ND_HIP(hipSetDevice(P->device));
   try {
-    apply_adj_into(P, f, c, nrhs, scratch_addr(P->device), nch, P->stream);
+    apply_adj_into(P, f, c, nrhs, scratch_addr(P->device), NOALLOC_SCRATCH_BYTES, P->stream);
   } catch (...) {
     if (switch_dev) (void)hipSetDevice(cur);
     throw;
@@ -403,13 +424,17 @@ void apply_adj_noalloc(Plan* P, const double2* f, double2* c, int nrhs) {
   if (switch_dev) ND_HIP(hipSetDevice(cur));
 }
 
-// Partial buffer of the library path: at most 256 MiB (n = 512: 32 chunks of
-// 4 MiB per right-hand side), held by the plan and grown on demand.
-constexpr size_t ADJ_PART_CAP = size_t(256) << 20;
+// Partials of the library path: at most 256 MiB (n = 512: 32 chunks of 4 MiB
+// per right-hand side), held by the plan and grown on demand.  Plans that share
+// a memory cap with their factors, batches (many plans' worth of partials), and
+// plans whose large buffer the device cannot hold keep to the base's chunks of
+// one vector of all coefficients.
 
 void apply_adj(Plan* P, const double2* f, double2* c, int nrhs, hipStream_t s) {
-  const int nch = std::max(1, adj_chunks(P, nrhs, ADJ_PART_CAP));
-  const size_t need = sizeof(double2) * (size_t)P->Ntot * (size_t)nrhs * (size_t)nch;
+  const size_t small =
+      sizeof(double2) * (size_t)P->Ntot * (size_t)nrhs * (size_t)adj_base_chunks(P, nrhs);
+  size_t budget = P->arena.cap || P->probs.size() > 1 || P->adj_small ? small : ADJ_PART_CAP;
+  size_t need = adj_part_need(P, nrhs, budget);
   if (need > P->adj_part_bytes) {
     if (P->adj_part) {
       ND_HIP(hipStreamSynchronize(s));   // earlier launches may still read it
@@ -417,10 +442,18 @@ void apply_adj(Plan* P, const double2* f, double2* c, int nrhs, hipStream_t s) {
     }
     P->adj_part = nullptr;
     P->adj_part_bytes = 0;
-    P->adj_part = (double2*)P->arena.alloc(need);
+    try {
+      P->adj_part = (double2*)P->arena.alloc(need);
+    } catch (const Error& e) {
+      if (budget == small || e.status != NUDFT2_E_NOMEM) throw;
+      P->adj_small = true;
+      budget = small;
+      need = adj_part_need(P, nrhs, budget);
+      P->adj_part = (double2*)P->arena.alloc(need);
+    }
     P->adj_part_bytes = need;
   }
-  apply_adj_into(P, f, c, nrhs, P->adj_part, nch, s);
+  apply_adj_into(P, f, c, nrhs, P->adj_part, budget, s);
 }
 
 }  // namespace nd

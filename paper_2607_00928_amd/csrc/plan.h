@@ -92,9 +92,11 @@ struct Plan {
   int64_t* colperm = nullptr;      // quadtree column index (global) -> natural index (global)
   ApplyProb* d_aprob = nullptr;
   // partial sums of the adjoint apply (one coefficient vector per row chunk
-  // and right-hand side), grown on demand from the arena
+  // and right-hand side of the problem being applied), grown on demand from
+  // the arena; adj_small: the device could not hold the larger buffer
   double2* adj_part = nullptr;
   size_t adj_part_bytes = 0;
+  bool adj_small = false;
   NufftState nufft;
   int* d_tile_off = nullptr;       // apply row-tile prefix (nprob + 1)
   int apply_tiles = 0;

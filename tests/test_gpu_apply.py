@@ -77,6 +77,31 @@ def test_adjoint_tile_edges(nx, ny, M, nrhs):
         plan.close()
 
 
+@pytest.mark.parametrize("sizes,nrhs,mib", [
+    # a batch of uneven problems: 49 MiB of partials for the largest count of
+    # row chunks over all coefficients
+    ([(96, 96), (32, 128), (64, 48), (128, 128), (48, 96), (32, 32), (128, 64), (96, 48),
+      (64, 64), (128, 32), (48, 48), (96, 128), (32, 64), (64, 96), (48, 128), (128, 96)], 1, 110),
+    ([(32, 32)] * 5 + [(2, 2), (128, 96)], 3, 40),
+    ([(96, 160)], 3, 36),         # 30 chunks of 720 KiB
+])
+def test_adjoint_partials_under_a_memory_cap(sizes, nrhs, mib):
+    # points and orderings take some 100 bytes a point; the partials have to fit
+    # beside them, and every problem's chunks cover its rows
+    rng = np.random.default_rng(len(sizes))
+    pts = [rng.random((4 * nx * ny, 2)) for nx, ny in sizes]
+    off = np.cumsum([0] + [p.shape[0] for p in pts])
+    g = complex_normal(rng, (nrhs, off[-1]))
+    plan = nd.BatchPlan(pts, [s[0] for s in sizes], [s[1] for s in sizes], mem_cap=mib << 20)
+    got = plan.apply_adj(torch.from_numpy(g).to(dev())).cpu().numpy().reshape(nrhs, -1)
+    plan.close()
+    c0 = 0
+    for (nx, ny), p, a, b in zip(sizes, pts, off, off[1:]):
+        ref = onu.apply_adj(p, g[:, a:b], nx, ny).reshape(nrhs, -1)
+        assert np.max(np.abs(got[:, c0:c0 + nx * ny] - ref)) < 1e-13 * np.max(np.abs(ref)), (nx, ny)
+        c0 += nx * ny
+
+
 def test_apply_full_size_sampled():
     # n = 512, M = 1024^2: compare 2000 sampled rows of A c and 64 sampled
     # coefficients of A^* f with the oracle evaluated one by one.
