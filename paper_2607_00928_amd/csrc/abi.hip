@@ -217,7 +217,7 @@ static void test_copy(int nb, const int32_t* dims, const int32_t* ld, const int6
                             (const cplx<TS>*)ptrs[2 * i], (cplx<TD>*)ptrs[2 * i + 1],
                             ct[i] != 0};
   DescPool pool;
-  pool.init(1 << 20, nullptr);
+  pool.init(1 << 20, nullptr, 64 << 20);
   copy_batched<TD, TS>(pool, d);
   pool.sync_reset();
 }

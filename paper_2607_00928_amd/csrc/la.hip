@@ -3563,18 +3563,25 @@ void copy_batched(DescPool& pool, const std::vector<CopyDesc<TD, TS>>& d) {
       maxcnt = std::max<int64_t>(maxcnt, (int64_t)q.m * q.n);
     }
   }
-  if (!pl.empty())
-    with_descs(pool, pl.data(), pl.size(), [&](auto dd) {
-      const unsigned gx = copy_grid_x((maxcnt + 2047) / 2048, pl.size());
-      hipLaunchKernelGGL((copy_kernel<TD, TS, decltype(dd)>), dim3(gx, (unsigned)pl.size()),
-                         dim3(256), 0, pool.stream, dd);
+  // a launch per 32768 of a list (grid.y holds at most 65536): a level's
+  // conversions are up to six blocks a node
+  constexpr size_t chunk = 32768;
+  for (size_t s0 = 0; s0 < pl.size(); s0 += chunk) {
+    const size_t n = std::min(chunk, pl.size() - s0);
+    with_descs(pool, pl.data() + s0, n, [&](auto dd) {
+      const unsigned gx = copy_grid_x((maxcnt + 2047) / 2048, n);
+      hipLaunchKernelGGL((copy_kernel<TD, TS, decltype(dd)>), dim3(gx, (unsigned)n), dim3(256), 0,
+                         pool.stream, dd);
     });
-  if (!ct.empty())
-    with_descs(pool, ct.data(), ct.size(), [&](auto dd) {
-      const unsigned gx = copy_grid_x(maxtiles, ct.size());
-      hipLaunchKernelGGL((copy_ct_kernel<TD, TS, decltype(dd)>), dim3(gx, (unsigned)ct.size()),
-                         dim3(256), 0, pool.stream, dd);
+  }
+  for (size_t s0 = 0; s0 < ct.size(); s0 += chunk) {
+    const size_t n = std::min(chunk, ct.size() - s0);
+    with_descs(pool, ct.data() + s0, n, [&](auto dd) {
+      const unsigned gx = copy_grid_x(maxtiles, n);
+      hipLaunchKernelGGL((copy_ct_kernel<TD, TS, decltype(dd)>), dim3(gx, (unsigned)n), dim3(256),
+                         0, pool.stream, dd);
     });
+  }
   ND_HIP(hipGetLastError());
 }
 

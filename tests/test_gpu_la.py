@@ -1120,3 +1120,22 @@ def test_geqrf_dependent_columns(prec, graded):
         print(f"dependent qr {i} {m}x{n} prec{prec}: recon {err:.1e} orth {orth:.1e}")
         assert err < 50 * TOL[prec] * np.sqrt(m)
         assert orth < 50 * TOL[prec] * np.sqrt(m)
+
+
+def test_copy_lists_longer_than_a_launch():
+    """70 000 conversions (and as many conjugate transposes) in one call, as a
+    level of a batch of thousands of small problems has: more than one launch
+    holds in grid.y.  Exact."""
+    n = 70000
+    S = torch.randn((n, 4), dtype=torch.complex64, device=DEV)
+    D = torch.zeros((2 * n, 4), dtype=torch.complex128, device=DEV)
+    src = S.data_ptr() + 32 * np.arange(n, dtype=np.int64)
+    ptr = np.stack([np.tile(src, 2), D.data_ptr() + 64 * np.arange(2 * n, dtype=np.int64)], axis=1)
+    a1, p1 = i32(np.full(4 * n, 2))
+    a2, p2 = i32(np.full(4 * n, 2))
+    a3, p3 = i64(ptr.ravel())
+    a4, p4 = i32(np.repeat([0, 1], n))
+    assert lib.nudft2_test_copy(0, 1, 2 * n, p1, p2, p3, p4) == 0, lib.nudft2_last_error()
+    assert torch.equal(D[:n], S.to(torch.complex128))
+    ct = S.reshape(n, 2, 2).transpose(1, 2).conj().reshape(n, 4)
+    assert torch.equal(D[n:], ct.to(torch.complex128))
