@@ -2339,19 +2339,20 @@ __global__ void pchol_finish_kernel(const PcholDesc* __restrict__ descs, const i
 // packed by columns ((r, c), r <= c, at c (c + 1) / 2 + r), with the inverted
 // diagonal; each wave then substitutes with one right-hand side at a time in
 // registers (lane l holds rows l and l + 64) and broadcasts each solved entry
-// with a lane read.  A workgroup takes TRS_RHS right-hand sides, so the triangle
-// is staged once for all of them (a workgroup per right-hand side staged it 128
-// times for an inversion: 17 ms of the n = 512 factorization).
+// with a lane read.  A workgroup takes `per` right-hand sides, 4 (one a wave) to
+// TRS_RHS, so the triangle is staged once for all of them (a workgroup per
+// right-hand side staged it 128 times for an inversion: 17 ms of the n = 512
+// factorization).
 constexpr int TRS_B = 128;
 constexpr int TRS_RHS = 32;
 
 template <typename T, bool CT, class DS>
-__global__ __launch_bounds__(256) void trsv_lds_kernel(DS descs) {
+__global__ __launch_bounds__(256) void trsv_lds_kernel(DS descs, int per) {
   using C2 = cplx<T>;
   __shared__ C2 Rp[TRS_B * (TRS_B + 1) / 2];
   __shared__ C2 inv[TRS_B];
   const TrsDesc<T> d = descs[blockIdx.x];
-  const int rhs0 = blockIdx.y * TRS_RHS;
+  const int rhs0 = blockIdx.y * per;
   if (rhs0 >= d.nrhs || d.k <= 0) return;
   const int k = min(d.k, TRS_B);
   const int ne = k * (k + 1) / 2;
@@ -2384,7 +2385,7 @@ __global__ __launch_bounds__(256) void trsv_lds_kernel(DS descs) {
   }
   __syncthreads();
   const int lane = tid & 63;
-  for (int rhs = rhs0 + (tid >> 6); rhs < min(d.nrhs, rhs0 + TRS_RHS); rhs += 4) {
+  for (int rhs = rhs0 + (tid >> 6); rhs < min(d.nrhs, rhs0 + per); rhs += 4) {
     C2* b = d.B + (int64_t)rhs * d.ldb;
     C2 x0 = lane < k ? b[lane] : mk<T>(0, 0);
     C2 x1 = lane + 64 < k ? b[lane + 64] : mk<T>(0, 0);
@@ -3395,11 +3396,19 @@ static void trsv_small(DescPool& pool, const std::vector<TrsDesc<T>>& d, bool ct
   for (auto& q : d) maxr = std::max(maxr, q.nrhs);
   with_descs(pool, d.data(), d.size(), [&](auto dd) {
     using DS = decltype(dd);
-    const dim3 grid((unsigned)d.size(), (unsigned)((maxr + TRS_RHS - 1) / TRS_RHS));
+    // right-hand sides a workgroup: as few as one round of the device (one or,
+    // in FP32, two triangles a CU) takes, since a wave solves its own one after
+    // the other (one system of order 128 with 32: 85 us with 4, 261 with 32; 300
+    // of order 100 with 40: 634 us with one, 240 with 32)
+    const int64_t slots = (int64_t)device_cus() * (sizeof(T) == 4 ? 2 : 1);
+    const int64_t want = ((int64_t)d.size() * maxr + slots - 1) / slots;
+    const int per = (int)std::min<int64_t>(TRS_RHS, (want + 3) / 4 * 4);
+    const dim3 grid((unsigned)d.size(), (unsigned)((maxr + per - 1) / per));
     if (ct)
-      hipLaunchKernelGGL((trsv_lds_kernel<T, true, DS>), grid, dim3(256), 0, pool.stream, dd);
+      hipLaunchKernelGGL((trsv_lds_kernel<T, true, DS>), grid, dim3(256), 0, pool.stream, dd, per);
     else
-      hipLaunchKernelGGL((trsv_lds_kernel<T, false, DS>), grid, dim3(256), 0, pool.stream, dd);
+      hipLaunchKernelGGL((trsv_lds_kernel<T, false, DS>), grid, dim3(256), 0, pool.stream, dd,
+                         per);
   });
   ND_HIP(hipGetLastError());
 }

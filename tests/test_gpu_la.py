@@ -488,6 +488,31 @@ def test_trsv(prec, ct):
         assert np.abs(X - ref).max() < 100 * TOL[prec] * max(1, np.abs(ref).max())
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("ct", [0, 1])
+@pytest.mark.parametrize("nb,k,nr", [(1, 128, 33), (3, 65, 5), (40, 30, 41), (150, 20, 65)])
+def test_trsv_right_hand_sides(prec, ct, nb, k, nr):
+    # 4 to 32 right-hand sides a workgroup, by the list's length; uneven lists.
+    # A wave's solution is backward stable: an error of k roundings, times the
+    # condition (below 8 for this triangle)
+    rng = np.random.default_rng(50 + nb)
+    ns = [max(1, nr - i % 7) for i in range(nb)]
+    R = np.triu(crandn(rng, k, k), 1) / k + (2 + np.abs(crandn(rng, k))) * np.eye(k)
+    Bs = [crandn(rng, k, n) for n in ns]
+    tR = to_dev(R, prec)
+    tBs = [to_dev(B, prec) for B in Bs]
+    a1, p1 = i32(sum([[k, n] for n in ns], []))
+    a2, p2 = i32([k, k] * nb)
+    a3, p3 = i64(sum([[tR.data_ptr(), t.data_ptr()] for t in tBs], []))
+    assert lib.nudft2_test_trsv(prec, nb, p1, p2, p3, ct) == 0, lib.nudft2_last_error()
+    Rr = from_dev(tR, k, k).astype(np.complex128)
+    eps = 2.0 ** -24 if prec else 2.0 ** -53
+    for B, t, n in zip(Bs, tBs, ns):
+        B = B.astype(CT[prec][0]).astype(np.complex128)
+        ref = np.linalg.solve(Rr.conj().T if ct else Rr, B)
+        assert np.abs(from_dev(t, k, n) - ref).max() < 8 * k * eps * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("prec", [0, 1, 2])
 @pytest.mark.parametrize("opa,opb", [(0, 0), (1, 0), (0, 1), (1, 1)])
 def test_gemm_large_batch(prec, opa, opb):
