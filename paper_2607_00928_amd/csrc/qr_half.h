@@ -43,6 +43,19 @@ constexpr int QRH_W = QR_HB + QR_NB;
 constexpr size_t QRH_XY = (size_t)QR_NB * QRH_W * sizeof(double2);
 constexpr size_t QRH_A1 = (size_t)QR_NB * QRH_W * sizeof(float2);
 constexpr int QRH_MAXC = 32;             // most row chunks (partial Grams) of a problem
+// Tall panels, from QRH_TALL steps on in lists of few problems: more chunks, of
+// four steps or more, with their partials in the pool's stream scratch (the
+// workspace holds 13 at 128 columns).  A step of the row pass takes a workgroup
+// 19 us, the sum of a chunk's partials 1 us, so a panel of 100 000 x 128 spent
+// 2.3 ms on 13 of the device's 256 CUs.
+constexpr int QRH_TALL = 64;
+constexpr int QRH_MAXC_TALL = 128;
+constexpr int QRH_TALL_SPLIT = 2048;     // rows from which a split takes a row pass
+struct QrhPart {
+  double2* tall;   // nullptr: the partials lie in the problems' scratch
+  size_t stride;   // elements of a problem's partials there
+  int maxc;        // most chunks of a problem
+};
 
 // A problem's scratch: the block W, W2, S of geqrf's workspace, which only the
 // steps between halves use.  xy: [X | Y] (QR_NB x QRH_W, leading dimension
@@ -62,7 +75,8 @@ struct QrhScratch {
   double2* part;
   int ncw, cap;
 };
-__device__ inline QrhScratch qrh_scratch(const QRDesc<float>& d, int H0) {
+__device__ inline QrhScratch qrh_scratch(const QRDesc<float>& d, int prob, int H0,
+                                         const QrhPart& pp) {
   const size_t el = (size_t)2 * QR_OB * max(d.n, 1) + (size_t)QR_OB * QR_OB;
   char* base = (char*)(d.Tw - el);
   QrhScratch s;
@@ -75,12 +89,17 @@ __device__ inline QrhScratch qrh_scratch(const QRDesc<float>& d, int H0) {
   s.part = (double2*)(base + QRH_XY + QRH_A1 + 2 * QRH_ST);
   s.cap = (int)((el * sizeof(float2) - QRH_XY - QRH_A1 - 2 * QRH_ST) /
                 (sizeof(double2) * QR_NB * s.ncw));
+  if (pp.tall) {
+    s.part = pp.tall + prob * pp.stride;
+    s.cap = (int)(pp.stride / (QR_NB * s.ncw));
+  }
   return s;
 }
 // row chunks of `rows` rows: their number and the steps of each
 __host__ __device__ inline int qrh_chunks(int rows, int maxc, int cap, int& per) {
   const int sub = (rows + QRH_ROWS - 1) / QRH_ROWS;
-  const int mc = maxc < cap ? maxc : cap;
+  int mc = maxc < cap ? maxc : cap;
+  if (mc > QRH_MAXC) mc = sub / 4 > QRH_MAXC ? (sub / 4 < mc ? sub / 4 : mc) : QRH_MAXC;
   per = (sub + mc - 1) / mc;
   per = per > 1 ? per : 1;
   return (sub + per - 1) / per;
@@ -164,7 +183,7 @@ __device__ __forceinline__ void qrh_gram_store(double2* part, int ctile, const d
 // rows.  Without PREV: the first panel's Gram alone (j1 = H0).
 template <bool PREV, class AS>
 __global__ __launch_bounds__(256, 2) void qr_half_rows_kernel(
-    const QRDesc<float>* __restrict__ descs, AS active, int H0, int j1, int maxc) {
+    const QRDesc<float>* __restrict__ descs, AS active, int H0, int j1, QrhPart pp) {
   __shared__ float2 An[QR_HB][QRH_LD];
   const QRDesc<float> d = descs[active[blockIdx.y]];
   const int kmin = min(d.m, d.n), hend = min(d.n, H0 + QR_HB);
@@ -175,9 +194,9 @@ __global__ __launch_bounds__(256, 2) void qr_half_rows_kernel(
   const bool next = (!PREV || jb == QR_NB) && j1 < min(kmin, H0 + QR_HB);
   const int jbn = next ? min(QR_NB, kmin - j1) : 0;
   const int rows = d.m - rb;
-  const QrhScratch sc = qrh_scratch(d, H0);
+  const QrhScratch sc = qrh_scratch(d, active[blockIdx.y], H0, pp);
   int per;
-  const int nck = qrh_chunks(rows, maxc, sc.cap, per);
+  const int nck = qrh_chunks(rows, pp.maxc, sc.cap, per);
   if ((int)blockIdx.x >= max(nck, 1)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = lane & 15, hi = lane >> 4;
@@ -272,14 +291,14 @@ __global__ __launch_bounds__(256, 2) void qr_half_rows_kernel(
 // the final columns), and the new Gram against the half's remaining columns.
 template <class AS>
 __global__ __launch_bounds__(256, 2) void qr_half_split_kernel(
-    const QRDesc<float>* __restrict__ descs, AS active, int H0, int j0, int maxc, int pass) {
+    const QRDesc<float>* __restrict__ descs, AS active, int H0, int j0, QrhPart pp, int pass) {
   __shared__ float2 An[QR_HB][QRH_LD];
   const QRDesc<float> d = descs[active[blockIdx.y]];
   const int jb = min(QR_NB, min(d.m, d.n) - j0), rows = d.m - j0;
   const int nc = min(d.n, H0 + QR_HB) - j0, ctile = (nc + 15) / 16;
-  const QrhScratch sc = qrh_scratch(d, H0);
+  const QrhScratch sc = qrh_scratch(d, active[blockIdx.y], H0, pp);
   int per;
-  const int nck = qrh_chunks(rows, maxc, sc.cap, per);
+  const int nck = qrh_chunks(rows, pp.maxc, sc.cap, per);
   if ((int)blockIdx.x >= nck || sc.st[pass & 1]->js == jb) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = lane & 15, hi = lane >> 4;
@@ -608,7 +627,7 @@ __device__ inline void qrh_gram_rows(const float2* V, int nv, const float2* B, i
 // a split panel is finished here, by workgroup 0.
 template <class AS>
 __global__ __launch_bounds__(256, 2) void qr_half_factor_kernel(
-    const QRDesc<float>* __restrict__ descs, AS active, int H0, int j0, int maxc, int pass,
+    const QRDesc<float>* __restrict__ descs, AS active, int H0, int j0, QrhPart pp, int pass,
     bool more) {
   __shared__ QrhLds S;
   const QRDesc<float> d = descs[active[blockIdx.y]];
@@ -630,7 +649,7 @@ __global__ __launch_bounds__(256, 2) void qr_half_factor_kernel(
   }
   if (blockIdx.x > 0 && (int)blockIdx.x >= nq) return;
   const bool first = blockIdx.x == 0;
-  const QrhScratch sc = qrh_scratch(d, H0);
+  const QrhScratch sc = qrh_scratch(d, active[blockIdx.y], H0, pp);
   const int rows = d.m - j0;
   QrhState* const out = sc.st[pass & 1];
   const QrhState* const in = sc.st[(pass & 1) ^ 1];
@@ -640,7 +659,7 @@ __global__ __launch_bounds__(256, 2) void qr_half_factor_kernel(
     return;
   }
   int per;
-  const int nck = qrh_chunks(rows, maxc, sc.cap, per);
+  const int nck = qrh_chunks(rows, pp.maxc, sc.cap, per);
   // sum of the partial Grams' columns c0 .. c0 + 31 (n of them) into B
   auto load_gram = [&](Blk B, int c0, int n) {
     double2 s[4];
@@ -864,21 +883,33 @@ static void qr_half_panels(DescPool& pool, const QRDesc<float>* dd,
                            int H0, bool graded) {
   // about 2048 row chunks over the batch (two workgroups a CU, four rounds);
   // fewer, longer chunks leave CUs idle, more add partial Grams to sum
-  const int maxc = std::max(1, std::min(QRH_MAXC, 2048 / std::max<int>(1, (int)act.size())));
+  int tallest = 0;
+  for (int i : act) tallest = std::max(tallest, d[i].m - H0);
+  const int nact = std::max<int>(1, (int)act.size());
+  QrhPart pp{nullptr, 0, std::max(1, std::min(QRH_MAXC, 2048 / nact))};
+  const size_t room = kGemmPartBytes / (sizeof(double2) * d.size());
+  if (tallest > QRH_TALL * QRH_ROWS && room / (QR_NB * QR_HB) >= QRH_MAXC &&
+      2048 / nact > QRH_MAXC) {
+    pp.tall = (double2*)pool.stream_scratch(kGemmPartBytes);
+    if (pp.tall) {
+      pp.stride = room;
+      pp.maxc = std::min(QRH_MAXC_TALL, 2048 / nact);
+    }
+  }
   auto rows_pass = [&](const std::vector<int>& a, int j1, bool prev) {
     int rows = 0;
     for (int i : a) rows = std::max(rows, d[i].m - (prev ? j1 - QR_NB : H0));
-    const int gx = std::max(1, std::min(maxc, (rows + QRH_ROWS - 1) / QRH_ROWS));
+    const int gx = std::max(1, std::min(pp.maxc, (rows + QRH_ROWS - 1) / QRH_ROWS));
     with_descs(pool, a.data(), a.size(), [&](auto as) {
       using AS = decltype(as);
       // covers every problem's chunks: at most maxc, and no more than steps
       dim3 grid((unsigned)gx, (unsigned)a.size());
       if (prev)
         hipLaunchKernelGGL((qr_half_rows_kernel<true, AS>), grid, dim3(256), 0, pool.stream, dd,
-                           as, H0, j1, maxc);
+                           as, H0, j1, pp);
       else
         hipLaunchKernelGGL((qr_half_rows_kernel<false, AS>), grid, dim3(256), 0, pool.stream, dd,
-                           as, H0, j1, maxc);
+                           as, H0, j1, pp);
     });
   };
   rows_pass(act, H0, false);
@@ -900,19 +931,21 @@ static void qr_half_panels(DescPool& pool, const QRDesc<float>* dd,
     // idle (each repeats the panel's factorization), else one per problem
     const unsigned nw = (int)cur.size() * nq <= device_cus() ? std::max(nq, 1) : 1;
     // graded lists: two further passes for the panels that split, each a row
-    // pass and a factorization (some 20 us where no panel needs them; a split
-    // finished by one workgroup takes 0.2 to 1 ms)
-    const int passes = graded ? 3 : 1;
-    const int gx = std::max(1, std::min(maxc, (mr + QRH_ROWS - 1) / QRH_ROWS));
+    // pass and a factorization (some 20 us where no panel needs them); tall
+    // panels: one, from four times the height on two (a split finished by one
+    // workgroup takes 0.2 ms for 600 rows, 0.5 for 4000; 60 000 x 256 of rank 20
+    // spent 16 of 24 ms so)
+    const int passes = graded || mr > 4 * QRH_TALL_SPLIT ? 3 : mr > QRH_TALL_SPLIT ? 2 : 1;
+    const int gx = std::max(1, std::min(pp.maxc, (mr + QRH_ROWS - 1) / QRH_ROWS));
     with_descs(pool, cur.data(), cur.size(), [&](auto as) {
       using AS = decltype(as);
       for (int p = 0; p < passes; ++p) {
         const bool more = p + 1 < passes;
         hipLaunchKernelGGL((qr_half_factor_kernel<AS>), dim3(nw + 1, (unsigned)cur.size()),
-                           dim3(256), 0, pool.stream, dd, as, H0, j0, maxc, p, more);
+                           dim3(256), 0, pool.stream, dd, as, H0, j0, pp, p, more);
         if (more)
           hipLaunchKernelGGL((qr_half_split_kernel<AS>), dim3((unsigned)gx, (unsigned)cur.size()),
-                             dim3(256), 0, pool.stream, dd, as, H0, j0, maxc, p);
+                             dim3(256), 0, pool.stream, dd, as, H0, j0, pp, p);
       }
     });
     rows_pass(cur, j0 + QR_NB, true);

@@ -1164,3 +1164,50 @@ def test_copy_lists_longer_than_a_launch():
     assert torch.equal(D[:n], S.to(torch.complex128))
     ct = S.reshape(n, 2, 2).transpose(1, 2).conj().reshape(n, 4)
     assert torch.equal(D[n:], ct.to(torch.complex128))
+
+
+@pytest.mark.parametrize("shapes", [
+    # one tall problem: as many row chunks as steps / 4, and the most
+    [(4097, 33), (70, 40)], [(8193, 40), (5000, 64), (100, 128)], [(33001, 64)],
+    # lists whose partial Grams fill the scratch, and one too long for it
+    [(4200, 48)] * 32, [(4200, 40)] * 33,
+])
+@pytest.mark.parametrize("rank", [None, 9])
+def test_geqrf_tall_panels(shapes, rank):
+    """FP32 panels over thousands of rows, full rank and of rank 9 (their panels
+    split): V's and T's reflectors times R give back A column by column, and
+    are unitary.  A column is rounded to FP32 once per panel and half, and each
+    of its at most n reflectors adds a rounding of the column's norm: 8 n 2^-24."""
+    rng = np.random.default_rng(90)
+    keep, mn, ld, ptr, cases = [], [], [], [], []
+    for m, n in shapes:
+        k = min(m, n)
+        A = crandn(rng, m, n) if rank is None else crandn(rng, m, rank) @ crandn(rng, rank, n)
+        tA = to_dev(A, 1)
+        A = tA.to(torch.complex128).clone()
+        tR = torch.full((n, k), 7.0, dtype=torch.complex64, device=DEV)
+        tT = torch.zeros((k * k,), dtype=torch.complex64, device=DEV)
+        keep += [tA, tR, tT]
+        cases.append((A, tA, tR, tT, m, n, k))
+        mn += [m, n]
+        ld += [m, k]
+        ptr += [t.data_ptr() for t in (tA, tR, tT)]
+    a1, p1 = i32(mn)
+    a2, p2 = i32(ld)
+    a3, p3 = i64(ptr)
+    assert lib.nudft2_test_geqrf(1, len(shapes), p1, p2, p3) == 0, lib.nudft2_last_error()
+    for A, tA, tR, tT, m, n, k in cases:
+        V = tA.to(torch.complex128)[:k].T.contiguous()          # m x k
+        T = tT.to(torch.complex128).reshape(k, k).T.contiguous()
+        R = tR.to(torch.complex128).T.contiguous()              # k x n
+        E = torch.zeros((m, n), dtype=torch.complex128, device=DEV)
+        E[:k] = R
+        QR = E - V @ (T @ (V.conj().T.contiguous() @ E))
+        nrm = torch.linalg.vector_norm(A, dim=1)
+        err = (torch.linalg.vector_norm(QR.T - A, dim=1) / nrm).max().item()
+        orth = V.conj().T.contiguous() @ V
+        wy = T + T.conj().T - T.conj().T.contiguous() @ orth @ T   # zero where Q is unitary
+        un = torch.linalg.matrix_norm(V @ wy, 2).item() if m < 10000 else wy.abs().max().item()
+        print(f"tall {m}x{n}: {err:.1e} {un:.1e}")
+        bound = 8 * 2.0 ** -24 * n
+        assert err < bound and un < bound
