@@ -218,6 +218,15 @@ __global__ __launch_bounds__(NT) void interp_kernel(const double* __restrict__ p
 // and 2w kernel values a point): the whole type 1 transform of n = 512, M =
 // 2^20, w = 14 takes 0.38 ms.  Adding every point's w^2 cells to the grid with
 // FP64 atomics took 12.7 ms, bound by the atomics (4 10^8 of them).
+//
+// Runs too short for their windows go point by point: 64 points' weights in
+// LDS, then one atomic add per point and cell over all threads (the narrow grid
+// 512 x 2, M = 1024, one point a box: 36 us, as windows 484; a thread per point
+// took 196).  In units of one atomic a batch of a window costs SP_BATCH and a
+// point's weights SP_POINT beside its w^2 cells.  The line follows both sides:
+// 512 x 512, M = 1.5 N, boxes of 6 points, w = 8: 1.87 ms as windows, 0.90 by
+// points; w = 14: 2.00 ms as windows, 5.4 with every point's cells added alone.
+constexpr int SP_BATCH = 600, SP_POINT = 12;
 constexpr int SP_C = 48;      // window cells per axis: three 16-cell tiles
 constexpr int SP_T = SP_C / 16;
 constexpr int SP_B = 64;      // points per batch, 16 a wave
@@ -229,6 +238,7 @@ struct SpreadLds {
     double2 red[SP_C][SP_C];      // the waves' sums
   };
   double2 f[SP_B];
+  int2 cell[SP_B];                // a point's first cells
   int key[SP_CHUNK];
   int end;
 };
@@ -252,6 +262,15 @@ __global__ __launch_bounds__(NT, 2) void spread_kernel(const double* __restrict_
   for (int p = tid; p < cnt; p += NT)
     S.key[p] = (leaf_bin(pts2d[2 * (base + p)], L) << 16) | leaf_bin(pts2d[2 * (base + p) + 1], L);
   const double cx = (double)q.nfx / (double)(1 << L), cy = (double)q.nfy / (double)(1 << L);
+  // first cell that a box's points reach, and how many
+  auto reach = [&](int b, double c, int& l0) {
+    l0 = (int)ceil(b * c - 0.5 * w);
+    return (int)ceil((b + 1) * c - 0.5 * w) - l0 + w;
+  };
+  auto few = [&](int n, int nx, int ny) {
+    const int nb = ((nx + SP_C - 1) / SP_C) * ((ny + SP_C - 1) / SP_C) * ((n + SP_B - 1) / SP_B);
+    return n * (SP_POINT + w * w) < SP_BATCH * nb + nx * ny;
+  };
   for (int s0 = 0; s0 < cnt;) {
     // the run [s0, s1) of points in the box of point s0
     __syncthreads();
@@ -264,12 +283,70 @@ __global__ __launch_bounds__(NT, 2) void spread_kernel(const double* __restrict_
         break;
       }
     __syncthreads();
-    const int s1 = S.end;
-    // first cells the box's points reach, and how many
-    const int bx = key >> 16, by = key & 0xffff;
-    const int lx = (int)ceil(bx * cx - 0.5 * w), ly = (int)ceil(by * cy - 0.5 * w);
-    const int nx = (int)ceil((bx + 1) * cx - 0.5 * w) - lx + w;
-    const int ny = (int)ceil((by + 1) * cy - 0.5 * w) - ly + w;
+    int s1 = S.end;
+    int lx, ly;
+    const int nx = reach(key >> 16, cx, lx), ny = reach(key & 0xffff, cy, ly);
+    if (few(s1 - s0, nx, ny)) {
+      // with the short runs that follow
+      __syncthreads();
+      if (tid == 0) S.end = cnt;
+      __syncthreads();
+      for (int p = s1 + tid; p < cnt; p += NT) {
+        const int k = S.key[p];   // ends of p's run: a box's points are consecutive
+        int a = s1, z = p;
+        while (a < z) {
+          const int m = (a + z) >> 1;
+          if (S.key[m] == k) z = m;
+          else a = m + 1;
+        }
+        int y = p + 1;
+        z = cnt;
+        while (y < z) {
+          const int m = (y + z) >> 1;
+          if (S.key[m] == k) y = m + 1;
+          else z = m;
+        }
+        int l0;
+        if (!few(y - a, reach(k >> 16, cx, l0), reach(k & 0xffff, cy, l0))) {
+          atomicMin(&S.end, p);
+          break;
+        }
+      }
+      __syncthreads();
+      s1 = S.end;
+      for (int b0 = s0; b0 < s1; b0 += SP_B) {
+        const int nb = min(SP_B, s1 - b0);
+        __syncthreads();
+        {
+          // four threads a point, every fourth cell of each axis
+          const int p = tid >> 2, c0 = tid & 3;
+          if (p < nb) {
+            const int64_t s = base + b0 + p;
+            if (c0 == 0) S.f[p] = fr[perm2d[s]];
+            const double ihw = 2.0 / (double)w;
+            const double tx = pts2d[2 * s] * (double)q.nfx;
+            const double ty = pts2d[2 * s + 1] * (double)q.nfy;
+            const int x0 = (int)ceil(tx - 0.5 * w), y0 = (int)ceil(ty - 0.5 * w);
+            if (c0 == 0) S.cell[p] = make_int2(x0, y0);
+            for (int i = c0; i < w; i += 4) {
+              S.w[0][p][i] = es_kernel((double)(x0 + i) - tx, beta, ihw);
+              S.w[1][p][i] = es_kernel((double)(y0 + i) - ty, beta, ihw);
+            }
+          }
+        }
+        __syncthreads();
+        for (int e = tid; e < nb * w * w; e += NT) {
+          const int p = e / (w * w), r = e - p * (w * w), i = r / w, j = r - i * w;
+          const int x = (S.cell[p].x + i) & (q.nfx - 1), y = (S.cell[p].y + j) & (q.nfy - 1);
+          const double t = S.w[0][p][i] * S.w[1][p][j];
+          double* o = gr + 2 * ((int64_t)x * q.nfy + y);
+          atomic_addg(o, t * S.f[p].x);
+          atomic_addg(o + 1, t * S.f[p].y);
+        }
+      }
+      s0 = s1;
+      continue;
+    }
     for (int wx0 = 0; wx0 < nx; wx0 += SP_C)
       for (int wy0 = 0; wy0 < ny; wy0 += SP_C) {
         dbl4 ar[SP_T][SP_T], ai[SP_T][SP_T];

@@ -137,3 +137,27 @@ def test_spreading_boxes(nx, ny, M, leaf, tol):
     plan.close()
     ref = onu.apply_adj(pts, F, nx, ny)
     assert max(rel(c[i], ref[i]) for i in range(2)) < 10 * tol
+
+
+@pytest.mark.parametrize("nx,ny,M,leaf,tol,cluster", [
+    (512, 2, 1500, 16, 1e-12, 0),     # a point or two a box
+    (2, 256, 600, 16, 1e-3, 0),
+    (64, 64, 4100, 2, 1e-12, 0),      # on the line between windows and points
+    (64, 32, 6000, 4, 1e-6, 0.5),     # long runs between short ones in a chunk
+    (128, 128, 17000, 64, 1e-2, 0.3), # windows of many cells, a narrow kernel
+    (32, 32, 1024, 2, 0.05, 0.9),
+])
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_spreading_short_runs(nx, ny, M, leaf, tol, cluster, nrhs):
+    """Type 1 where leaf boxes hold too few points for their windows, beside
+    full ones (the clustered share), within the transform's 10 tol."""
+    rng = np.random.default_rng(41)
+    pts = rng.random((M, 2))
+    k = int(cluster * M)
+    pts[:k] = 0.61 + 0.02 * pts[:k]
+    F = complex_normal(rng, (nrhs, M))
+    plan = nd.Plan(pts, nx, ny, leaf=leaf)
+    c = plan.nufft_adj(torch.from_numpy(F).to(DEV), tol).cpu().numpy().reshape(nrhs, nx, ny)
+    plan.close()
+    ref = onu.apply_adj(pts, F, nx, ny)
+    assert max(rel(c[i], ref[i]) for i in range(nrhs)) < 10 * tol
