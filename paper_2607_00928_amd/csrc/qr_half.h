@@ -50,7 +50,6 @@ constexpr int QRH_MAXC = 32;             // most row chunks (partial Grams) of a
 // 2.3 ms on 13 of the device's 256 CUs.
 constexpr int QRH_TALL = 64;
 constexpr int QRH_MAXC_TALL = 128;
-constexpr int QRH_TALL_SPLIT = 2048;     // rows from which a split takes a row pass
 struct QrhPart {
   double2* tall;   // nullptr: the partials lie in the problems' scratch
   size_t stride;   // elements of a problem's partials there
@@ -931,11 +930,11 @@ static void qr_half_panels(DescPool& pool, const QRDesc<float>* dd,
     // idle (each repeats the panel's factorization), else one per problem
     const unsigned nw = (int)cur.size() * nq <= device_cus() ? std::max(nq, 1) : 1;
     // graded lists: two further passes for the panels that split, each a row
-    // pass and a factorization (some 20 us where no panel needs them); tall
-    // panels: one, from four times the height on two (a split finished by one
-    // workgroup takes 0.2 ms for 600 rows, 0.5 for 4000; 60 000 x 256 of rank 20
-    // spent 16 of 24 ms so)
-    const int passes = graded || mr > 4 * QRH_TALL_SPLIT ? 3 : mr > QRH_TALL_SPLIT ? 2 : 1;
+    // pass and a factorization (some 20 us where no panel needs them: 0.7% of the
+    // n = 256 solution if every list over 4096 rows had one); tall panels of other
+    // lists one (a split finished by one workgroup takes 0.2 ms for 600 rows, 0.5
+    // for 4000; 60 000 x 256 of rank 20 spent 16 of 24 ms so)
+    const int passes = graded ? 3 : mr > 2 * QRH_TALL * QRH_ROWS ? 2 : 1;
     const int gx = std::max(1, std::min(pp.maxc, (mr + QRH_ROWS - 1) / QRH_ROWS));
     with_descs(pool, cur.data(), cur.size(), [&](auto as) {
       using AS = decltype(as);
