@@ -1132,16 +1132,17 @@ __global__ __launch_bounds__(256) void gemm_skinny_c16_kernel(DS descs, int spli
   }
 }
 
-// Products with 2 or 5 to 16 columns, B not transposed (sweeps with several
-// right-hand sides): bound by latency, then by the read of A.  A workgroup
-// takes 16 RT rows of C; its four waves take every fourth chunk of 16 k, each
-// with up to four chunks (8 to 16 KB of A) in flight, straight from memory in
-// the matrix instructions' layout (lane group g of a chunk holds k = 4 g ..
-// 4 g + 3: op C reads 4 consecutive k of a column, op N 16 rows of one), and
-// their sums meet in LDS.  4 products 256 x 16 x 256: 7.8 us; the 64 x 64
-// tiles, a quarter of their columns used and 16 workgroups in the launch, took
-// 19.4.  With `part`, k range z of splits stores its tile at
-// part[((y splits + z) gridDim.x + x) 256 RT] for gemm_n16_reduce_kernel.
+// Products with few columns, B not transposed (sweeps with several right-hand
+// sides; n16_pays below says which): bound by latency, then by the read of A.  A
+// workgroup takes 16 RT rows of C; its four waves take every fourth chunk of 16
+// k, each with up to four chunks (8 to 16 KB of A) in flight, straight from
+// memory in the matrix instructions' layout.  Lane group g of a chunk holds k =
+// 2 g, 2 g + 1, 2 g + 8 and 2 g + 9: two 16-byte loads of a column for op C and
+// for B, 16 rows of each of the four k for op N.  The waves' sums meet in LDS.
+// 4 products 256 x 16 x 256: 7.8 us; the 64 x 64 tiles, a quarter of their
+// columns used and 16 workgroups in the launch, took 19.4.  With `part`, k range
+// z of splits stores its tile at part[((y splits + z) gridDim.x + x) 256 RT] for
+// gemm_n16_reduce_kernel.
 // Elements 0, 1, 8, 9: 16-byte loads for float2, which global memory takes at
 // any element's alignment
 typedef float gf4u __attribute__((ext_vector_type(4), aligned(8)));
@@ -2684,8 +2685,60 @@ static int device_cus() {
   return cus;
 }
 
-// Products with at most 16 columns on gemm_n16_kernel; false where the k
-// ranges' sums have no scratch (the caller's tiles add them atomically).
+// Whether gemm_n16_kernel takes a launch whose B is not transposed (and whose
+// outputs are not Hermitian), by its sizes and the workgroups w it would have.
+// Both sides were timed over m = 8 to 30 000, n = 2 to 128, k = 16 to 20 000 and
+// 1 to 2000 products (op C, above 16 columns: m <= 32).  The kernel's workgroups
+// are short, so its rivals win where k is too small to pay for four waves and
+// there are many workgroups; below, us of this kernel / of the rival.
+//  * Up to 8 columns the rivals are the kernels that take one column at a time:
+//    op C from 5 columns and k = 96 (FP64 192, 8 columns 96) on (64 of 256 x 5 x 64 15 / 13,
+//    x 96 15 / 15, of 256 x 8 x 256 18 / 30), op N in FP32 from 2 columns (4 of
+//    256 x 2 x 256 7.6 / 14; 500 of 64 x 2 x 64 34 / 27), in FP64 from 5.
+//  * From 9 columns the rival is the 64 x 64 tile, which reads B better: small k
+//    over many workgroups is its own (500 of 64 x 16 x 64 36 / 31, of 64 x 16 x
+//    256 42 / 48).
+//  * A^H B with few rows of C (the products V^H C of a panel's update) in blocks
+//    of 16 columns: the 64 x 64 tiles leave a workgroup or two to walk the whole
+//    k (32 x 100 x 512 FP64 14 / 92), but fill the device themselves from some
+//    hundred workgroups on, the sooner the more of their 64 columns are used (60
+//    of 32 x 32 x 1500 27 / 37, 100 of 32 x 64 x 1500 75 / 46; FP64 42 / 97 and
+//    128 / 105); a list of blocks that no longer fits the kernel's arguments
+//    costs a copy where the products alone would have fit (16 of 32 x 64 x 64
+//    11 / 9).
+template <typename T>
+static bool n16_pays(Op opA, int m, int n, int k, int64_t nd) {
+  constexpr bool f64 = sizeof(T) == 8;
+  const int64_t cb = ceil_div(n, 16), w = ceil_div(m, 16) * cb * nd;
+  if (n <= 16) {
+    if (opA == OpC) {
+      if (n < 5) return false;
+      if (n <= 8)
+        return k >= (f64 && n < 8 ? 192 : 96) && !(f64 && n <= 6 && k >= 3000 && w > 16 && w <= 128);
+      return k >= (f64 ? 64 : 128) || w <= 8 * (int64_t)k;
+    }
+    if (n < 5)
+      return !f64 && n >= 2 && k >= 64 && w < 8192 &&
+             (k >= 192 || w <= 4 * (int64_t)(n - 1) * k);
+    return k >= 192 || w <= 512;
+  }
+  if (opA != OpC || m > 32 || n > 128 || nd * cb > 32768) return false;
+  const int64_t args = kArgDescBytes / sizeof(GemmDesc<T>);
+  const bool copy = nd <= args && nd * cb > args;
+  if (k >= 1024) {
+    if (!f64) return w <= (cb == 2 ? 512 : 128);
+    return cb == 2 ? w <= 8 * (int64_t)k : cb <= 4 ? w <= 512 : w <= 4 * (int64_t)k;
+  }
+  if (!f64) return k >= (copy ? 192 : 64) && w <= (copy ? 1 : 2) * (int64_t)k;
+  return k >= (copy ? 64 : 16) && w <= (k < 96 ? 2 : 8) * (cb == 2 ? 2 : 1) * (int64_t)k;
+}
+
+// Products with at most 16 columns on gemm_n16_kernel.  Half the device's CUs
+// or fewer and a long k: k ranges of 256 or more, about four workgroups a CU
+// (256 x 16 x 3000 12.6 us, unsplit 25; from 256 workgroups on the ranges cost
+// what they save: 16 of 256 x 16 x 3000 33 and 32).  Their sums go through the
+// pool's stream scratch; without it k up to 2048 runs unsplit, and false for
+// longer ones leaves the launch to the caller's tiles, which add atomically.
 template <typename T>
 static bool n16_batched(DescPool& pool, const std::vector<GemmDesc<T>>& sub, Op opA, int maxm,
                         int maxn, int maxk) {
@@ -2694,18 +2747,17 @@ static bool n16_batched(DescPool& pool, const std::vector<GemmDesc<T>>& sub, Op 
   const int t16 = (maxm + 15) / 16;
   const bool two = (int64_t)t16 * n >= 4096;
   const int rt = two ? 2 : 1, gx = (t16 + rt - 1) / rt;
-  // k ranges of 256 or more, to about four workgroups a CU
   const int64_t wgs = (int64_t)gx * n, slots = 4 * (int64_t)device_cus();
   const size_t tile_b = (size_t)256 * rt * sizeof(cplx<T>);
   int splits = 1;
   cplx<T>* part = nullptr;
-  if (maxk >= 1024 && wgs <= slots / 2) {
+  if (maxk >= (sizeof(T) == 8 ? 512 : 1024) && wgs <= slots / 8) {
     const int64_t sp = std::min<int64_t>({(slots + wgs - 1) / wgs, maxk / 256,
                                           (int64_t)(kGemmPartBytes / (tile_b * (size_t)wgs))});
     if (sp >= 2) {
       part = (cplx<T>*)pool.stream_scratch(kGemmPartBytes);
-      if (!part) return false;
-      splits = (int)sp;
+      if (part) splits = (int)sp;
+      else if (maxk > 2048) return false;
     }
   }
   double fl = 0;
@@ -2812,35 +2864,17 @@ void gemm_batched(DescPool& pool, const std::vector<GemmDesc<T>>& d, Op opA, Op 
       smallmn_batched<T>(pool, sub, maxm, maxn, maxk);
       continue;
     }
-    // Columns from which gemm_n16_kernel beats the one-column-at-a-time kernels
-    // below (us, new / old: op N 4 products 3000 x 2 x 256 11 / 15, but 256 of 900 x
-    // 2 x 256 125 / 103 and FP64 512 of 240 x 3 x 240 184 / 146; op C FP32 16 of
-    // 564^2 with 4 columns 20 / 18, with 5 19 / 26) and the sizes: op N over many
-    // row tiles needs a k that keeps the four waves busy (1408 of 167 x 8 x 95: 137
-    // / 74, 64 of 281 x 8 x 238: 22 / 73)
-    const int64_t tiles = (int64_t)ceil_div(maxm, 16) * (int64_t)n;
-    const int n16 = sizeof(T) == 4 && opA == OpN && tiles < 8192 ? 2 : 5;
-    const bool k16 = opA == OpC || maxk >= 192 || tiles <= 512;
-    if (splits_force == 0 && maxn >= n16 && maxn <= 16 && opB == OpN && k16 && !lower_any &&
-        n16_batched<T>(pool, sub, opA, maxm, maxn, maxk))
-      continue;
+    const bool n16 = splits_force == 0 && opB == OpN && !lower_any &&
+                     n16_pays<T>(opA, maxm, maxn, maxk, (int64_t)n);
+    if (n16 && maxn <= 16 && n16_batched<T>(pool, sub, opA, maxm, maxn, maxk)) continue;
     if (maxn <= SK_N && opB == OpN) {
       skinny_batched<T>(pool, sub, opA, maxm, maxn, maxk, force);
       continue;
     }
-    // A^H B with few rows of C (the products V^H C of a panel's update): blocks of
-    // 16 columns on gemm_n16_kernel, which reads A once a block; the 64 x 64 tiles
-    // leave a workgroup or two to walk the whole k (32 x 96 x 512 FP64: 15 / 94 us,
-    // 16 of them 22 / 95, FP32 15 / 34).  With many blocks the tiles fill the device
-    // themselves and win for short k (128 products 32 x 96 x 128: 45 / 38, FP32 33 /
-    // 20), in FP32 for any (k = 1500: 102 / 93; FP64 178 / 237).
-    const int cb = ceil_div(maxn, 16);
-    const int64_t nblk = (int64_t)n * cb;
-    const int cbk = nblk <= (sizeof(T) == 8 ? 128 : 32) ? 16 : nblk <= 128 ? 64 : 256;
-    if (splits_force == 0 && opA == OpC && opB == OpN && maxm <= 32 && maxn > 16 && maxn <= 128 &&
-        maxk >= cbk && nblk <= (sizeof(T) == 8 ? 65535 : 512) && !lower_any) {
+    if (n16 && maxn > 16) {
+      // blocks of 16 columns, A read once a block
       std::vector<GemmDesc<T>> blk;
-      blk.reserve(nblk);
+      blk.reserve(n * ceil_div(maxn, 16));
       for (const auto& g : sub)
         for (int j = 0; j < g.n; j += 16) {
           GemmDesc<T> q = g;

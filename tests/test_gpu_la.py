@@ -1211,3 +1211,45 @@ def test_geqrf_tall_panels(shapes, rank):
         print(f"tall {m}x{n}: {err:.1e} {un:.1e}")
         bound = 8 * 2.0 ** -24 * n
         assert err < bound and un < bound
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("opa,m,n,k,nb", [
+    # each side of the lines between gemm_n16_kernel, the one-column kernels and
+    # the tiles, with ragged sizes
+    (1, 70, 5, 95, 3), (1, 70, 5, 97, 3), (1, 70, 8, 191, 3), (1, 70, 6, 192, 3),
+    (1, 65, 9, 63, 30), (1, 65, 9, 31, 60), (1, 65, 16, 127, 200), (1, 65, 16, 129, 200),
+    (0, 65, 2, 64, 7), (0, 65, 3, 63, 7), (0, 65, 4, 65, 80), (0, 65, 5, 191, 120),
+    (0, 65, 16, 193, 120),
+    (1, 31, 17, 63, 3), (1, 31, 48, 65, 9), (1, 31, 17, 100, 30), (1, 9, 128, 200, 20),
+    (1, 31, 100, 1030, 3), (1, 31, 33, 1030, 40), (1, 31, 20, 1100, 150),
+    # k ranges from half the CUs down, and none above
+    (1, 250, 9, 511, 8), (1, 250, 9, 520, 8), (1, 250, 9, 1025, 9), (0, 250, 7, 1030, 8),
+])
+def test_gemm_route_lines(prec, opa, m, n, k, nb):
+    """Entrywise as test_gemm_up_to_16_columns, on both sides of every line of
+    the choice of kernel."""
+    rng = np.random.default_rng(61)
+    ct = CT[prec][0]
+    A = crandn(rng, *((m, k) if opa == 0 else (k, m))).astype(ct)
+    tA = to_dev(A, prec)
+    Bs = [crandn(rng, k, n).astype(ct) for _ in range(min(nb, 3))]
+    tBs = [to_dev(B, prec) for B in Bs]
+    C0 = torch.randn((n, m), dtype=CT[prec][1], device=DEV)
+    tC = C0.repeat(nb, 1, 1)
+    a1, p1 = i32([m, n, k] * nb)
+    a2, p2 = i32([A.shape[0], k, m] * nb)
+    a3, p3 = i64(sum([[tA.data_ptr(), tBs[i % len(tBs)].data_ptr(), tC[i].data_ptr()]
+                      for i in range(nb)], []))
+    alpha, beta = 0.8 - 0.5j, 0.5
+    st = lib.nudft2_test_gemm(prec, opa, 0, nb, p1, p2, p3, alpha.real, alpha.imag, beta)
+    assert st == 0, lib.nudft2_last_error()
+    oA = (A if opa == 0 else A.conj().T).astype(np.complex128)
+    c0 = C0.cpu().numpy().T
+    eps = 2.0 ** -24 if prec else 2.0 ** -53
+    got = tC.cpu().numpy()
+    for i in range(nb):
+        B = Bs[i % len(Bs)]
+        ref = alpha * (oA @ B.astype(np.complex128)) + beta * c0
+        scale = abs(alpha) * (np.abs(oA) @ np.abs(B)) + beta * np.abs(c0)
+        assert (np.abs(got[i].T - ref) / scale).max() < 8 * eps * np.sqrt(k), i
