@@ -144,7 +144,8 @@ static void test_gemm(int opA, int opB, int nb, const int32_t* mnk, const int32_
                        (const cplx<T>*)ptrs[3 * i + 1], (cplx<T>*)ptrs[3 * i + 2], (T)ar,
                        (T)ai, (T)beta};
   DescPool pool;
-  pool.init(std::max<size_t>(1 << 20, sizeof(GemmDesc<T>) * (size_t)nb * 2 + 4096), nullptr);
+  pool.init(1 << 20, nullptr, 64 << 20);
+  if (ms) pool.stream_scratch(kGemmPartBytes);   // kept by a program's pool: not timed
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (ms) {
     ND_HIP(hipEventCreate(&e0));

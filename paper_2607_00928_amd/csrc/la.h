@@ -90,6 +90,9 @@ struct GemmDesc {
 // the same output matrix (their tiles run concurrently).  A descriptor with
 // lower = 1 leaves the tiles strictly above the diagonal untouched (for
 // Hermitian products whose consumer reads the lower triangle only).
+// Products with few columns (or A^H B with few rows of C, in blocks of 16
+// columns) take kernels of 16 columns or one column at a time (n16_pays); the
+// rest the 64 x 64 tiles.
 // Where the output tiles cannot fill the device, the k loop is shared out
 // over workgroups (atomic accumulation into a pre-scaled C): when the
 // autotuned table (gemm_tuning.inc, written by tune_gemm.py) or else a
@@ -99,7 +102,7 @@ struct GemmDesc {
 // m <= 32 the 32 x 128 or 16/32-square tiles of the small-output kernels.
 // splits_force > 0 forces that many plain k splits on the 64 x 64 tiles
 // (used by the tuner); -1 runs the tile kernel unsplit, without the table;
-// -2 takes the heuristic without the table (the tuner's baseline); -3 takes
+// -2 takes the library's choice without the table (the tuner's baseline); -3 takes
 // stream-K wherever it applies; -4 takes the partial-tile split wherever the
 // pool has room for it; -5 / -6 force the 32 x 128 / square small-output
 // tiles (E_INVAL where the shapes do not allow them).

@@ -2864,8 +2864,9 @@ void gemm_batched(DescPool& pool, const std::vector<GemmDesc<T>>& d, Op opA, Op 
       smallmn_batched<T>(pool, sub, maxm, maxn, maxk);
       continue;
     }
-    const bool n16 = splits_force == 0 && opB == OpN && !lower_any &&
-                     n16_pays<T>(opA, maxm, maxn, maxk, (int64_t)n);
+    // a tuned split of the class comes first
+    const bool n16 = (splits_force == 0 || splits_force == -2) && !(tt && tt->tile == 0) &&
+                     opB == OpN && !lower_any && n16_pays<T>(opA, maxm, maxn, maxk, (int64_t)n);
     if (n16 && maxn <= 16 && n16_batched<T>(pool, sub, opA, maxm, maxn, maxk)) continue;
     if (maxn <= SK_N && opB == OpN) {
       skinny_batched<T>(pool, sub, opA, maxm, maxn, maxk, force);

@@ -1213,6 +1213,36 @@ def test_geqrf_tall_panels(shapes, rank):
         assert err < bound and un < bound
 
 
+@pytest.mark.parametrize("prec,opa,m,n,k,nb", [
+    (2, 1, 256, 16, 256, 4), (2, 0, 256, 3, 256, 4), (0, 1, 100, 12, 700, 2),
+    (2, 1, 32, 96, 512, 2), (0, 1, 20, 33, 600, 3),     # blocks of 16 columns
+])
+def test_gemm_choice_without_the_table(prec, opa, m, n, k, nb):
+    """Code -2 is the library's choice but for the tuned table (the tuner's
+    baseline): where the table has no entry it is code 0, bit for bit; code 1
+    keeps the 64 x 64 tiles or the one-column kernels, to rounding."""
+    rng = np.random.default_rng(60)
+    cols = lambda X: to_dev(X, prec)
+    ms = [[cols(crandn(rng, *s)) for s in (((m, k) if opa == 0 else (k, m)), (k, n))]
+          for _ in range(nb)]
+    a1, p1 = i32([m, n, k] * nb)
+    a2, p2 = i32([m if opa == 0 else k, k, m] * nb)
+    out = {}
+    for code in (0, -2, 1):
+        out[code] = torch.zeros((nb, n, m), dtype=CT[prec][1], device=DEV)
+        a3, p3 = i64(sum([[A.data_ptr(), B.data_ptr(), out[code][i].data_ptr()]
+                          for i, (A, B) in enumerate(ms)], []))
+        assert lib.nudft2_test_gemm_cfg(prec, opa, 0, nb, p1, p2, p3, 1.0, 0.5, 0.0, code,
+                                        None) == 0, lib.nudft2_last_error()
+    assert torch.equal(out[0], out[-2])
+    eps = 2.0 ** -24 if prec else 2.0 ** -53
+    for i, (A, B) in enumerate(ms):
+        scale = abs(1 + 0.5j) * ((A.abs() if opa else A.abs().T).to(torch.float64)
+                                 @ B.abs().T.to(torch.float64))   # m x n of |op(A)| |B|
+        err = ((out[0][i] - out[1][i]).T.abs() / scale).max().item()
+        assert err < 16 * eps * np.sqrt(k)
+
+
 @pytest.mark.parametrize("prec", [0, 1, 2])
 @pytest.mark.parametrize("opa,m,n,k,nb", [
     # each side of the lines between gemm_n16_kernel, the one-column kernels and
