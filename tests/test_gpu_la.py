@@ -1283,3 +1283,71 @@ def test_gemm_route_lines(prec, opa, m, n, k, nb):
         ref = alpha * (oA @ B.astype(np.complex128)) + beta * c0
         scale = abs(alpha) * (np.abs(oA) @ np.abs(B)) + beta * np.abs(c0)
         assert (np.abs(got[i].T - ref) / scale).max() < 8 * eps * np.sqrt(k), i
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("opa", [0, 1])
+@pytest.mark.parametrize("beta", [0.0, 0.5, 1.0])
+@pytest.mark.parametrize("n,code,shapes", [
+    # one column, by the list's longest k: 16 lanes a row of C (op C) up to 512, a
+    # wave a row up to 2048, a workgroup a row above; op N with a k split from 512
+    (1, 0, [(1, 1), (300, 511), (257, 0), (33, 512), (5000, 64)]),
+    (1, 0, [(300, 513), (64, 1023), (5, 9)]),
+    (1, 0, [(300, 2047), (7, 1)]),
+    (1, 0, [(77, 2049), (200, 9001), (5, 4097)]),
+    (1, 0, [(64, 40000), (1, 9)]),
+    # as many workgroups as fill the device: 256 rows each (op N)
+    (1, 0, [(3, 5)] * 1030),
+    (4, 0, [(3, 5)] * 1030),
+    # two to four columns (FP32 op N: below the 16-column kernel's k of 64)
+    (2, 0, [(300, 63), (17, 1), (1, 20)]),
+    (4, 0, [(130, 60), (64, 33), (9, 0)]),
+    # forced k splits keep the one-column kernels: 1, and 3 added atomically to a
+    # scaled C
+    (3, 1, [(300, 700), (70, 64), (1, 9)]),
+    (8, 1, [(300, 500), (257, 7), (17, 0)]),
+    (8, 1, [(17, 3000), (64, 513)]),
+    (2, 3, [(64, 9000), (17, 3000)]),
+    (8, 3, [(17, 3000), (300, 700), (5, 33)]),
+    (8, 3, [(40, 480), (3, 100)]),
+])
+def test_gemm_one_column_kernels(prec, opa, beta, n, code, shapes):
+    """The kernels of up to 8 columns, each reached by a list of its own (the
+    route goes by the list's largest sizes): entrywise as
+    test_gemm_up_to_16_columns."""
+    rng = np.random.default_rng(80 + 2 * prec + opa)
+    ct = CT[prec][0]
+    alpha = -0.4 + 1.1j
+    mats, keep, mnk, ld, ptr = [], [], [], [], []
+    uniq = {}
+    for i, (m, k) in enumerate(shapes):
+        nc = n if i % 3 < 2 else 1
+        if (m, k) not in uniq or len(shapes) < 100:
+            A = crandn(rng, *((m, k) if opa == 0 else (k, m))).astype(ct)
+            B, Cm = crandn(rng, k, nc).astype(ct), crandn(rng, m, nc).astype(ct)
+            ta, tb = (to_dev(X, prec) if X.size else torch.zeros(1, dtype=torch.complex128,
+                                                                 device=DEV) for X in (A, B))
+            uniq[(m, k)] = (A, B, Cm, ta, tb, nc)
+        A, B, Cm, ta, tb, nc = uniq[(m, k)]
+        tc = to_dev(Cm, prec)
+        keep += [ta, tb, tc]
+        mats.append((A, B, Cm, tc, nc))
+        mnk += [m, nc, k]
+        ld += [max(A.shape[0], 1), max(k, 1), m]
+        ptr += [ta.data_ptr(), tb.data_ptr(), tc.data_ptr()]
+    a1, p1 = i32(mnk)
+    a2, p2 = i32(ld)
+    a3, p3 = i64(ptr)
+    st = lib.nudft2_test_gemm_cfg(prec, opa, 0, len(shapes), p1, p2, p3, alpha.real, alpha.imag,
+                                  beta, code, None)
+    assert st == 0, lib.nudft2_last_error()
+    eps = 2.0 ** -24 if prec else 2.0 ** -53
+    for (m, k), (A, B, Cm, tc, nc) in zip(shapes, mats):
+        oA = (A if opa == 0 else A.conj().T).astype(np.complex128)
+        ref = alpha * (oA @ B.astype(np.complex128)) + beta * Cm.astype(np.complex128)
+        scale = abs(alpha) * (np.abs(oA) @ np.abs(B)) + beta * np.abs(Cm)
+        got = from_dev(tc, m, nc)
+        if k == 0 and beta == 0:
+            assert not got.any()
+            continue
+        assert (np.abs(got - ref) / scale).max() < 8 * eps * np.sqrt(max(k, 4)), (m, nc, k)

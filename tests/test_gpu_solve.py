@@ -153,6 +153,31 @@ def test_graph_replays_match_eager(prec, refine):
     assert rel(cg.reshape(-1, 48 * 32)[0], ref.reshape(-1)) < 1e-10
 
 
+@pytest.mark.parametrize("nrhs", [6, 16])
+def test_graph_replays_of_many_right_hand_sides(nrhs):
+    """Captured sweeps with several right-hand sides, over leaf boxes of more
+    than 1024 rows (products whose eager k ranges go through scratch that a
+    capture has not): the eager solution, replay after replay, with the program's
+    own work between them."""
+    pr = make_problem(64, 32, 192, 96, 0.3, 4)
+    rng = np.random.default_rng(33)
+    c = complex_normal(rng, (nrhs, 64, 32))
+    out = {}
+    for graph in (False, True):
+        plan = nd.Plan(pr.points, 64, 32, precision="fp32", eps=1e-2, ir_maxit=60, ir_tol=1e-13,
+                       graph=graph)
+        f = plan.apply(torch.from_numpy(c).to(DEV))
+        plan.factor()
+        out[graph] = []
+        for _ in range(3):
+            out[graph].append(plan.solve(f).cpu().numpy())
+            torch.linalg.vector_norm(f)
+        plan.close()
+    for got in out[True]:
+        assert rel(got, out[False][0]) < 1e-12
+        assert rel(got, c) < 1e-11
+
+
 def test_graph_adjoint_and_batch():
     """Graph-captured normal-equation iterations (solve_adj) and a batch plan's
     graph-captured solve agree with their eager counterparts."""
