@@ -1351,3 +1351,65 @@ def test_gemm_one_column_kernels(prec, opa, beta, n, code, shapes):
             assert not got.any()
             continue
         assert (np.abs(got - ref) / scale).max() < 8 * eps * np.sqrt(max(k, 4)), (m, nc, k)
+
+
+@pytest.mark.parametrize("prec,graded", [(0, False), (1, False), (1, True)])
+def test_geqrf_dependent_columns_to_rounding(prec, graded):
+    """Where panels hold columns nearly dependent on earlier ones, Q R = A and Q
+    unitary to a small multiple of the stored precision u, so that a panel split
+    too late shows: a panel's own errors are some 2 u (its Gram and blocks are
+    FP64, A, V, R and T are rounded once), those of k / 32 panels and of the
+    products that join them add like independent ones: 16 u sqrt(k) in all.
+    With splits at a thousandth of the digits (a square of the norm left at 4e-12
+    of the terms' in place of 4e-9) the panel's arithmetic gives 1.4e-5 for the
+    sums and 2.9e-5 for the Cauchy matrix, FP32's bound being 8e-6 and 9.5e-6."""
+    rng = np.random.default_rng(710 + prec)
+    u = 2.0 ** -24 if prec else 2.0 ** -53
+    mats = []
+    for m, n, r in [(353, 160, 20), (64, 48, 5), (129, 129, 60), (40, 200, 33), (5000, 64, 12)]:
+        mats.append(crandn(rng, m, r) @ crandn(rng, r, n) / r ** 0.5 + 4 * u * crandn(rng, m, n))
+    A = crandn(rng, 500, 130)
+    A[:, 7] = A[:, 3]
+    A[:, 40] = 0
+    A[:, 41] = 2j * A[:, 2] + 3 * A[:, 39]
+    A[:, 100:] = A[:, :30]
+    mats.append(A)
+    B = crandn(rng, 700, 70)      # sums: each column an earlier one and a little more
+    for j in range(1, 70):
+        B[:, j] = B[:, j - 1] + 10.0 ** -(j % 8) * B[:, j]
+    mats.append(B)
+    i = np.arange(400)[:, None] / 400
+    mats.append(1 / (i + np.arange(100) / 100 + 0.01 + 0.002j))   # Cauchy
+    keep, mn, ld, ptr = [], [], [], []
+    for A in mats:
+        m, n = A.shape
+        k = min(m, n)
+        tA = to_dev(A, prec)
+        keep.append((tA.to(torch.complex128).clone(), tA,
+                     torch.zeros((n, k), dtype=CT[prec][1], device=DEV),
+                     torch.zeros(k * k, dtype=CT[prec][1], device=DEV)))
+        mn += [m, n]
+        ld += [m, k]
+        ptr += [t.data_ptr() for t in keep[-1][1:]]
+    a1, p1 = i32(mn)
+    a2, p2 = i32(ld)
+    a3, p3 = i64(ptr)
+    geqrf = lib.nudft2_test_geqrf_graded if graded else lib.nudft2_test_geqrf
+    assert geqrf(prec, len(mats), p1, p2, p3) == 0, lib.nudft2_last_error()
+    for A, tV, tR, tT in keep:      # rows are columns
+        n, m = A.shape
+        k = min(m, n)
+        V = tV.to(torch.complex128)[:k].T.contiguous()
+        T = tT.to(torch.complex128).reshape(k, k).T.contiguous()
+        E = torch.zeros((m, n), dtype=torch.complex128, device=DEV)
+        E[:k] = tR.to(torch.complex128).T
+        QR = E - V @ (T @ (V.conj().T.contiguous() @ E))
+        nrm = torch.linalg.vector_norm(A, dim=1)
+        err = torch.linalg.vector_norm(QR.T - A, dim=1) / torch.where(nrm > 0, nrm, 1.0)
+        Q = torch.eye(m, k, dtype=torch.complex128, device=DEV)
+        Q = Q - V @ (T @ V[:k].conj().T.contiguous())
+        orth = (Q.conj().T.contiguous() @ Q
+                - torch.eye(k, dtype=torch.complex128, device=DEV)).abs().max().item()
+        print(f"dependent {m}x{n} prec{prec}: {err.max().item():.1e} {orth:.1e}")
+        assert err.max().item() < 16 * u * k ** 0.5, (m, n)
+        assert orth < 16 * u * k ** 0.5, (m, n)
