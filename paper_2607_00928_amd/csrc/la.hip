@@ -2000,7 +2000,7 @@ __global__ void pchol_init_kernel(const PcholDesc* __restrict__ descs, double* t
 // so no workgroup waits on another inside a launch.  Ties go to the lower
 // row.  state[b]: 1 = still running.
 constexpr int PC_ROWS = 256;
-constexpr int PC_WG_ROWS = 1536;
+constexpr int PC_WG_ROWS = 1536, PC_WG_ROWS_MANY = 1344;
 
 __device__ inline bool pc_better(double v, int i, double bv, int bi) {
   return v > bv || (v == bv && i >= 0 && (bi < 0 || i < bi));
@@ -3372,10 +3372,13 @@ void pchol_batched(DescPool& pool, const std::vector<PcholDesc>& d) {
   // One workgroup per Gram up to PC_WG_ROWS rows; from there its reads of the
   // panel's earlier columns cost as much as a launch per column over many
   // workgroups (8 Grams, us a column: order 825 6.8 / 10.0, 1233 10.1 / 11.7,
-  // 1600 12.6 / 12.6, 2040 20.6 / 16.2).  Panels of 64 where the Schur updates of
-  // the batch weigh more than those reads (128 Grams of order 1000: 43 us a
-  // column with panels of 32, 33 with 64; 8 of order 825: 6.8, 7.8).
-  const bool wg = maxw <= PC_WG_ROWS;
+  // 1600 12.6 / 12.6, 2040 20.6 / 16.2), in lists of a dozen or more, whose column
+  // launches fill the device, from PC_WG_ROWS_MANY on (ms at a rank of 0.3 of the
+  // order: 40 of 1300 8.9 / 8.7, 12 of 1500 6.8 / 6.7, 30 of 1500 11.4 / 9.7).
+  // Panels of 64 where the Schur updates of the batch weigh more than those reads
+  // (128 Grams of order 1000: 43 us a column with panels of 32, 33 with 64; 8 of
+  // order 825: 6.8, 7.8).
+  const bool wg = maxw <= ((int64_t)nb * maxw < 16384 ? PC_WG_ROWS : PC_WG_ROWS_MANY);
   const int panel = !wg ? PC_NB : (int64_t)nb * maxw >= 65536 ? PC_PANEL : PC_PANEL / 2;
   const int gsize = (maxw + PC_ROWS - 1) / PC_ROWS;
   const int64_t grid = (int64_t)nb * gsize;

@@ -431,6 +431,12 @@ def test_pchol_greedy(sizes):
             assert np.abs(L - Lw).max() <= 1e-9 * np.abs(Lw).max(), (n, rm, rk)
 
 
+@pytest.mark.parametrize("order", [1344, 1345])
+def test_pchol_greedy_in_long_lists(order):
+    # both sides of the line between one workgroup and a launch per column
+    test_pchol_greedy([(order, 70, 66)] + [(40, 40, 20)] * 12)
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("nb", [1, 43, 400])
 def test_qr_descriptor_lists_outgrow_the_pool(prec, nb):
