@@ -1856,7 +1856,7 @@ __global__ __launch_bounds__(WY_NT) void wy_merge_kernel(DS descs) {
   }
 }
 
-// wy_merge for FP32: the half's T in LDS as 32 x 32 blocks (128 KB with S's),
+// wy_merge for FP32 halves of three or four panels: the half's T in LDS as 32 x 32 blocks (128 KB with S's),
 // joined by doubling: two pairs of panels, then the two pairs, every product a
 // sum of 32 x 32 ones on the FP32 matrix cores, a 16 x 16 tile a wave.  One
 // global round trip in all; staging the operands step by step with the products
@@ -3195,13 +3195,22 @@ void geqrf_batched(DescPool& pool, const std::vector<QRDesc<T>>& din, void* ws, 
       }
       gemm_batched<T>(pool, g1, OpC, OpN);
       if (!wy.empty()) {
+        int kh = 0;
+        for (auto& q : wy) kh = std::max(kh, q.kb);
         with_descs(pool, wy.data(), wy.size(), [&](auto dw) {
-          if constexpr (std::is_same<T, float>::value)
-            hipLaunchKernelGGL((wy_merge_f32_kernel<decltype(dw)>), dim3((unsigned)wy.size()),
-                               dim3(1024), 0, pool.stream, dw);
-          else
-            hipLaunchKernelGGL((wy_merge_kernel<T, decltype(dw)>), dim3((unsigned)wy.size()),
-                               dim3(WY_NT), 0, pool.stream, dw);
+          // halves of at most two panels: the step by step kernel, several
+          // workgroups a CU (us step by step / by doubling in LDS, one a CU: 32
+          // columns 2 / 11, 1000 problems 10 / 50; 64: 9 / 12, 33 / 57; 96: 24 / 14,
+          // 88 / 70; 128: 49 / 16, 186 / 89)
+          if constexpr (std::is_same<T, float>::value) {
+            if (kh > 2 * QR_NB) {
+              hipLaunchKernelGGL((wy_merge_f32_kernel<decltype(dw)>), dim3((unsigned)wy.size()),
+                                 dim3(1024), 0, pool.stream, dw);
+              return;
+            }
+          }
+          hipLaunchKernelGGL((wy_merge_kernel<T, decltype(dw)>), dim3((unsigned)wy.size()),
+                             dim3(WY_NT), 0, pool.stream, dw);
         });
         ND_HIP(hipGetLastError());
       }

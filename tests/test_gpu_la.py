@@ -1359,6 +1359,14 @@ def test_gemm_one_column_kernels(prec, opa, beta, n, code, shapes):
         assert (np.abs(got - ref) / scale).max() < 8 * eps * np.sqrt(max(k, 4)), (m, nc, k)
 
 
+@pytest.mark.parametrize("shapes", [
+    [(50, 32), (20, 31), (9, 1)], [(100, 33), (70, 64), (40, 5)], [(80, 65), (90, 20), (70, 32)],
+])
+def test_geqrf_few_panels_a_half(shapes):
+    # one or two panels in the list's largest half, and three: T's merge
+    test_geqrf_tall_panels(shapes, None)
+
+
 @pytest.mark.parametrize("prec,graded", [(0, False), (1, False), (1, True)])
 def test_geqrf_dependent_columns_to_rounding(prec, graded):
     """Where panels hold columns nearly dependent on earlier ones, Q R = A and Q
