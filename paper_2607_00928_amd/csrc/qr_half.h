@@ -930,11 +930,11 @@ static void qr_half_panels(DescPool& pool, const QRDesc<float>* dd,
     // idle (each repeats the panel's factorization), else one per problem
     const unsigned nw = (int)cur.size() * nq <= device_cus() ? std::max(nq, 1) : 1;
     // graded lists: two further passes for the panels that split, each a row
-    // pass and a factorization (some 20 us where no panel needs them: 0.7% of the
-    // n = 256 solution if every list over 4096 rows had one); tall panels of other
-    // lists one (a split finished by one workgroup takes 0.2 ms for 600 rows, 0.5
-    // for 4000; 60 000 x 256 of rank 20 spent 16 of 24 ms so)
-    const int passes = graded ? 3 : mr > 2 * QRH_TALL * QRH_ROWS ? 2 : 1;
+    // pass and a factorization (some 30 us where no panel needs them, 2% of a
+    // factorization with leaves of 16 384 rows if theirs had one); the tallest
+    // panels of other lists one (a split finished by one workgroup takes 0.2 ms
+    // for 600 rows, 0.5 for 4000; 60 000 x 256 of rank 20 spent 16 of 24 ms so)
+    const int passes = graded ? 3 : mr > 8 * QRH_TALL * QRH_ROWS ? 2 : 1;
     const int gx = std::max(1, std::min(pp.maxc, (mr + QRH_ROWS - 1) / QRH_ROWS));
     with_descs(pool, cur.data(), cur.size(), [&](auto as) {
       using AS = decltype(as);
