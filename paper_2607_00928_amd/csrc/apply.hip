@@ -166,9 +166,10 @@ constexpr int AP = 32;     // points per fill of the phase tables
 // phases (some 70 instructions each) count in full beside 3072 clk of matrix
 // work a stage: their tables are filled for two stages at a time, each thread
 // the same number of entries (a fill per stage left a quarter of the threads
-// with four of them and the others waiting with two: 96 x 160, M = 23 040, three
-// right-hand sides 294 -> 272 us, 512 x 512, M = 393 216 13.9 -> 13.3 ms; three
-// workgroups a CU with smaller tables are slower, 316 us and 15.1 ms).
+// with four of them and the others waiting with two: with the empty blocks'
+// matrix instructions left out, 96 x 160, M = 23 040, three right-hand sides in
+// 56 chunks 283 -> 258 us, 512 x 512, M = 393 216 13.9 -> 13.3 ms; three
+// workgroups a CU with smaller tables were slower, 316 us and 15.1 ms).
 // part[(chunk nrhs + rhs) nx ny + kx ny + ky] =
 //     sum_{j in chunk} conj(Ax[j][kx]) f_j conj(Ay[j][ky])
 // for the chunk of rows [blockIdx.y rows, (blockIdx.y + 1) rows); every entry
@@ -317,8 +318,8 @@ int64_t adj_base_chunks(const Plan* P, int nrhs) {
 // its partial vector, about 40 rows' worth of products; no fewer than the
 // plan's base, whose smaller shares even out the end of a long launch; and no
 // more than the partials of one problem leave room for in `budget` bytes.
-// 96 x 160, M = 23 040, three right-hand sides takes 258 us in 56 chunks, 389
-// us (with slower phase tables) in the base's 12.
+// 96 x 160, M = 23 040, three right-hand sides takes 258 us in 56 chunks; with
+// the phase tables of a fill per stage it took 283 us in 56 and 389 in 12.
 int adj_chunks(const Problem& q, int nrhs, int64_t base, size_t budget) {
   const int64_t fill = std::min<int64_t>(ceil_div(q.M, ADJ_MIN_ROWS),
                                          ADJ_WG_TARGET / ((int64_t)adj_tiles(q) * nrhs));
@@ -353,9 +354,9 @@ void apply_adj_into(Plan* P, const double2* f, double2* c, int nrhs, double2* pa
     hipLaunchKernelGGL(apply_adj_kernel, grid, dim3(256), 0, s, P->pts_user, f, part, pr,
                        P->Mtot, rows, nrhs);
     const int64_t n = q.N() * nrhs;
-    hipLaunchKernelGGL(adj_reduce_kernel,
-                       dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (n + 255) / 256))),
-                       dim3(256), 0, s, part, c, pr, nchp, P->Ntot, nrhs);
+    const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(4096, (n + 255) / 256));
+    hipLaunchKernelGGL(adj_reduce_kernel, dim3((unsigned)gx), dim3(256), 0, s, part, c, pr, nchp,
+                       P->Ntot, nrhs);
   }
   ND_HIP(hipGetLastError());
 }

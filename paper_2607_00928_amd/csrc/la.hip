@@ -1465,8 +1465,8 @@ __global__ void gemm_prescale_kernel(DS descs) {
 // described in la.h.
 //
 // FP64 panel factorization (FP32 panels: qr_half.h): a group of gsize
-// workgroups factors one problem's panel; workgroup w of the group holds panel rows [w 128 R, (w+1) 128 R)
-// in registers.  Wave v of a workgroup owns the column group v / 2 (QP_CG
+// workgroups factors one problem's panel; workgroup w of the group holds panel
+// rows [w 128 R, (w+1) 128 R) in registers.  Wave v of a workgroup owns the column group v / 2 (QP_CG
 // consecutive columns) on the row half v % 2; lane l of it holds rows
 // half * 64 QP_R + l + 64 k (k < QP_R) of those columns, so loads and stores
 // are coalesced and the per-column sums reduce within the wave (DPP) to one
@@ -1528,7 +1528,7 @@ constexpr int QSCR = 3 * QS + 3 * QR_NB;   // rotating sums + rotating row copie
 constexpr int QP_NT = 1024;            // threads of a panel workgroup
 constexpr int QP_CG = 4;               // columns per thread
 // rows per lane: 2 x 4 complex FP64 values (32 VGPRs)
-template <typename T> struct QPanel { static constexpr int R = 2; };
+constexpr int QP_R = 2;
 
 // sum over the 64 lanes of a wave, valid in lane 63 (all lanes active)
 template <typename T>
@@ -1549,7 +1549,7 @@ __global__ __launch_bounds__(QP_NT) void qr_panel_kernel(
     const QRDesc<T>* __restrict__ descs, AS active, int nact, int j0, int gsize,
     cplx<T>* __restrict__ scratch, unsigned* __restrict__ bar, int* __restrict__ err) {
   using C2 = cplx<T>;
-  constexpr int R = QPanel<T>::R * RM;
+  constexpr int R = QP_R * RM;
   constexpr int HALF = 64 * R;           // rows of one row half
   constexpr int ROWS = 2 * HALF;         // rows of a workgroup
   static_assert(QP_NT / 64 == 2 * (QR_NB / QP_CG), "16 waves: 8 column groups x 2 row halves");
@@ -3050,7 +3050,7 @@ void qr_panel_launch(DescPool& pool, const QRDesc<T>* dd, const std::vector<int>
     // every workgroup of the grid is resident
     return std::max(1, device_cus() * std::min(std::max(per, 1), 1));
   }();
-  constexpr int rows = 128 * QPanel<T>::R;
+  constexpr int rows = 128 * QP_R;
   int gsize = std::max(1, (maxmr + rows - 1) / rows);
   // Twice the rows per workgroup (RM = 2): for panels taller than the device
   // holds otherwise, and for multi-workgroup panels when the halved groups

@@ -19,10 +19,11 @@
 // left in column j, g = x^H G x with x = X e_j before scaling, carries the
 // rounding of G's entries, about 1e-16 (sum_i |x_i| ||a_i||)^2.  Where that
 // exceeds 3e-8 g (half of FP32's rounding; QRH_LOSS) the panel is split: the
-// reflectors before column j are applied to the tails, and the rest goes on from a new Gram: by the row pass and another
-// factorization launch where the caller expects such panels (the face-split
-// generators of the first recompression stage, whose panels lose three to
-// seven digits), else by the factorization's workgroup itself.
+// reflectors before column j are applied to the tails, and the rest goes on
+// from a new Gram: by a row pass and another factorization launch where the
+// caller expects such panels (the face-split generators of the first
+// recompression stage, whose panels lose three to seven digits) and for the
+// tallest ones, else by the factorization's workgroup itself.
 //
 // Bound: the blocks' factorization by its chain of 32 dependent columns
 // (sqrt, reciprocal and two LDS round trips each), the row pass by the FP64
@@ -480,7 +481,7 @@ __device__ inline int qrh_factor(QrhLds& S, Tile& g, Tile& a, Tile& x, int js, i
     wx += dpp_get<0x128, 0xF>(wx);
     if (j > js && __builtin_amdgcn_readfirstlane((int)!(gjj >= QRH_LOSS * wx * wx))) break;
     // squared norm from the pivot on: gjj, and no less than |alpha|^2; beta =
-    // -sign(Re alpha) nrm, tau = 1 - conj(alpha) / beta, scal = 1 / (alpha - beta)
+    // -sign(Re alpha) nrm, tau = 1 - alpha / beta, scal = 1 / (alpha - beta)
     const double a2 = fma(al.x, al.x, al.y * al.y), nn = fmax(gjj, a2);
     const double rn = rsqrt64(nn), nrm = nn * rn, ax = fabs(al.x);
     const double id = rcp64(fma(2.0 * nrm, ax, nn + a2));   // 1 / |alpha - beta|^2
