@@ -3373,21 +3373,23 @@ void pchol_batched(DescPool& pool, const std::vector<PcholDesc>& d) {
   double* trace = (double*)pool.reserve(sizeof(double) * nb);
   int* state = (int*)pool.reserve(sizeof(int) * nb);
   hipLaunchKernelGGL(pchol_init_kernel, dim3(nb), dim3(256), 0, pool.stream, dd, trace, state);
-  int rmax = 0, maxw = 1;
+  int rmax = 0, maxw = 1, nlarge = 0;
   for (auto& q : d) {
     rmax = std::max(rmax, std::min(q.rmax, q.w));
     maxw = std::max(maxw, q.w);
+    nlarge += q.w > PC_WG_ROWS_MANY;
   }
   // One workgroup per Gram up to PC_WG_ROWS rows; from there its reads of the
   // panel's earlier columns cost as much as a launch per column over many
   // workgroups (8 Grams, us a column: order 825 6.8 / 10.0, 1233 10.1 / 11.7,
-  // 1600 12.6 / 12.6, 2040 20.6 / 16.2), in lists of a dozen or more, whose column
-  // launches fill the device, from PC_WG_ROWS_MANY on (ms at a rank of 0.3 of the
-  // order: 40 of 1300 8.9 / 8.7, 12 of 1500 6.8 / 6.7, 30 of 1500 11.4 / 9.7).
+  // 1600 12.6 / 12.6, 2040 20.6 / 16.2).  With a dozen Grams above
+  // PC_WG_ROWS_MANY the column launches fill the device and win there too (ms at
+  // a rank of 0.3 of the order: 12 of 1500 6.8 / 6.4, 30 of 1500 11.4 / 9.0; 40 of
+  // 1300 8.9 / 8.7; eight of up to 1500 beside smaller ones 9.5 / 11.0).
   // Panels of 64 where the Schur updates of the batch weigh more than those reads
   // (128 Grams of order 1000: 43 us a column with panels of 32, 33 with 64; 8 of
   // order 825: 6.8, 7.8).
-  const bool wg = maxw <= ((int64_t)nb * maxw < 16384 ? PC_WG_ROWS : PC_WG_ROWS_MANY);
+  const bool wg = maxw <= (nlarge < 12 ? PC_WG_ROWS : PC_WG_ROWS_MANY);
   const int panel = !wg ? PC_NB : (int64_t)nb * maxw >= 65536 ? PC_PANEL : PC_PANEL / 2;
   const int gsize = (maxw + PC_ROWS - 1) / PC_ROWS;
   const int64_t grid = (int64_t)nb * gsize;

@@ -431,10 +431,11 @@ def test_pchol_greedy(sizes):
             assert np.abs(L - Lw).max() <= 1e-9 * np.abs(Lw).max(), (n, rm, rk)
 
 
-@pytest.mark.parametrize("order", [1344, 1345])
-def test_pchol_greedy_in_long_lists(order):
-    # both sides of the line between one workgroup and a launch per column
-    test_pchol_greedy([(order, 70, 66)] + [(40, 40, 20)] * 12)
+@pytest.mark.parametrize("order,count", [(1344, 12), (1345, 11), (1345, 12)])
+def test_pchol_greedy_in_long_lists(order, count):
+    # both sides of the line between one workgroup and a launch per column, by
+    # the order and the number of Grams above it
+    test_pchol_greedy([(order, 40, 36)] * count + [(102, 40, 20)] * 3)
 
 
 @pytest.mark.parametrize("prec", [0, 1])
